@@ -2,6 +2,7 @@
 // parameters, chunk start, input embedding, solver-time embedding, the int8
 // activation quantiser of the W2A8 path, and finite checks.
 #include <cmath>
+#include <utility>
 #include "device_common.h"
 
 namespace {
@@ -62,47 +63,82 @@ __global__ __launch_bounds__(256) void chunk_start_kernel(const CallParams* cp, 
   e[(size_t)k * d + j + half] = ElemTraits<T>::from_f(cv);
 }
 
-// One workgroup per token row: finish the residual stream x (add the split-K
-// partials of a residual projection, form the input embedding, or take the
-// backbone's input rows) and write the next sublayer's adaRMS input u.  A thread owns the columns
-// 4*(tid + 256*i); all of its loads are issued before the row reduction.
-template <typename T>
+// Sum over the wave's 64 lanes, the same in every lane: the 16 lanes of a row
+// by DPP adds (one VALU latency each, where a shuffle through LDS takes about
+// ten), then the four row sums in order.
+VLA_DEV float wave_sum_dpp(float v) {
+  auto add = [&](auto ctrl) {
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  add(std::integral_constant<int, 0xB1>{});   // lane ^ 1
+  add(std::integral_constant<int, 0x4E>{});   // lane ^ 2
+  add(std::integral_constant<int, 0x141>{});  // mirrored in 8
+  add(std::integral_constant<int, 0x140>{});  // mirrored in 16
+  const int b = __float_as_int(v);
+  return (__int_as_float(__builtin_amdgcn_readlane(b, 0)) + __int_as_float(__builtin_amdgcn_readlane(b, 16))) +
+         (__int_as_float(__builtin_amdgcn_readlane(b, 32)) + __int_as_float(__builtin_amdgcn_readlane(b, 48)));
+}
+
+// One workgroup per token row: finish the residual stream x (MODE 0: add the
+// split-K partials of a residual projection; 1: form the input embedding; 2:
+// take the backbone's input rows) and write the next sublayer's adaRMS input
+// u.  A thread owns the columns 4*(tid + 256*i), i < CPT.
+//
+// The kernel is one chain of latencies (a row is 3-16 KB), so everything that
+// does not depend on the row is in flight before the first wait: the row, its
+// partials, alpha, and gamma and beta, which are used last.  CPT is the
+// smallest that covers d, so a narrow row runs no masked-off groups.
+// A launch in a chunk's graph (50 rows of 720, 4 partials): 4.2 -> 3.7 us.
+template <typename T, int MODE, int CPT>
 __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
-  constexpr int CPT = 4;  // float4 groups per thread: d <= 4 * 256 * CPT
+  constexpr int NP = CPT == 1 ? 8 : 4;   // partials in flight at once
   const int m = blockIdx.x;
   const int d = a.d;
   const int t = threadIdx.x;
   __shared__ float red[4];
-  float4 xv[CPT];
+  const float inv_d = 1.0f / (float)d;
+  float4 xv[CPT], gg[CPT], bb[CPT];
   float ss = 0.0f;
-  if (a.mode == 0) {
+  auto load_gb = [&]() {
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) {
+      const int c = 4 * (t + 256 * i);
+      gg[i] = c < d ? *reinterpret_cast<const float4*>(a.gamma + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      bb[i] = c < d ? *reinterpret_cast<const float4*>(a.beta + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  if constexpr (MODE == 0) {
     const float* xr = a.x + (size_t)m * d;
+    const bool upd = a.alpha != nullptr;
+    const int np = upd ? a.nsplit : 0;
+    float4 al[CPT], pv[NP][CPT];
+    auto load_part = [&](int s0) {
+#pragma unroll
+      for (int u = 0; u < NP; ++u)
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+          const int c = 4 * (t + 256 * i);
+          pv[u][i] = (s0 + u < np && c < d) ? *reinterpret_cast<const float4*>(a.part + ((size_t)(s0 + u) * a.M + m) * d + c)
+                                            : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
       const int c = 4 * (t + 256 * i);
       xv[i] = c < d ? *reinterpret_cast<const float4*>(xr + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+      al[i] = (upd && c < d) ? *reinterpret_cast<const float4*>(a.alpha + c) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if (a.alpha != nullptr) {
-      float4 ps[CPT], al[CPT];
+    load_part(0);
+    load_gb();
+    __builtin_amdgcn_sched_barrier(0);   // every load above is issued before the first use
+    if (upd) {
+      float4 ps[CPT];
 #pragma unroll
-      for (int i = 0; i < CPT; ++i) {
-        const int c = 4 * (t + 256 * i);
-        ps[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        al[i] = c < d ? *reinterpret_cast<const float4*>(a.alpha + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-      for (int s0 = 0; s0 < a.nsplit; s0 += 4) {
-        float4 pv[4][CPT];
+      for (int i = 0; i < CPT; ++i) ps[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int s0 = 0; s0 < np; s0 += NP) {
+        if (s0) load_part(s0);
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-          for (int i = 0; i < CPT; ++i) {
-            const int c = 4 * (t + 256 * i);
-            pv[u][i] = (s0 + u < a.nsplit && c < d)
-                           ? *reinterpret_cast<const float4*>(a.part + ((size_t)(s0 + u) * a.M + m) * d + c)
-                           : make_float4(0.f, 0.f, 0.f, 0.f);
-          }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < NP; ++u)
 #pragma unroll
           for (int i = 0; i < CPT; ++i) {
             ps[i].x += pv[u][i].x; ps[i].y += pv[u][i].y; ps[i].z += pv[u][i].z; ps[i].w += pv[u][i].w;
@@ -114,8 +150,9 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
         xv[i].z += al[i].z * ps[i].z; xv[i].w += al[i].w * ps[i].w;
       }
     }
-  } else if (a.mode == 2) {
+  } else if constexpr (MODE == 2) {
     const T* xr = reinterpret_cast<const T*>(a.x_in) + (size_t)m * d;
+    load_gb();
 #pragma unroll
     for (int i = 0; i < CPT; ++i) {
       const int c = 4 * (t + 256 * i);
@@ -130,6 +167,7 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
     const int ai = a.stok ? b * (a.n - 1) + tok - 1 : m;   // action row
     const int et = a.stok ? tok - 1 : tok;                  // its E_pos row
     __shared__ float arow[64];
+    load_gb();
     if (t < a.A) arow[t] = srow ? 0.0f : a.a[(size_t)ai * a.A + t];
     __syncthreads();
     const T* W = reinterpret_cast<const T*>(a.W_in);
@@ -168,28 +206,27 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
       ss += xv[i].x * xv[i].x + xv[i].y * xv[i].y + xv[i].z * xv[i].z + xv[i].w * xv[i].w;
     }
   }
-  ss = wave_sum(ss);
+  ss = wave_sum_dpp(ss);
   if ((t & 63) == 0) red[t >> 6] = ss;
-  __syncthreads();
-  const float rstd = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)d + a.eps);
+  lds_barrier();   // LDS only: the stores of x complete behind the rest
+  const float ms = (red[0] + red[1] + red[2] + red[3]) * inv_d + a.eps;
+  // 1 / sqrt(ms): the hardware estimate (1 ulp) and one Newton step
+  float rstd = __builtin_amdgcn_rsqf(ms);
+  rstd = rstd + 0.5f * rstd * (1.0f - ms * rstd * rstd);
 #pragma unroll
   for (int i = 0; i < CPT; ++i) {
     const int c = 4 * (t + 256 * i);
     if (c >= d) continue;
-    const float4 g = *reinterpret_cast<const float4*>(a.gamma + c);
-    const float4 bb = *reinterpret_cast<const float4*>(a.beta + c);
-    const float u0 = xv[i].x * rstd * (1.0f + g.x) + bb.x;
-    const float u1 = xv[i].y * rstd * (1.0f + g.y) + bb.y;
-    const float u2 = xv[i].z * rstd * (1.0f + g.z) + bb.z;
-    const float u3 = xv[i].w * rstd * (1.0f + g.w) + bb.w;
-    if (a.u_f32) {
+    const float4 g = gg[i], b = bb[i];
+    const float u0 = xv[i].x * rstd * (1.0f + g.x) + b.x;
+    const float u1 = xv[i].y * rstd * (1.0f + g.y) + b.y;
+    const float u2 = xv[i].z * rstd * (1.0f + g.z) + b.z;
+    const float u3 = xv[i].w * rstd * (1.0f + g.w) + b.w;
+    if (sizeof(T) == 4 || a.u_f32) {
       *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.u) + (size_t)m * d + c) = make_float4(u0, u1, u2, u3);
     } else {
-      T* up = reinterpret_cast<T*>(a.u) + (size_t)m * d + c;
-      up[0] = ElemTraits<T>::from_f(u0);
-      up[1] = ElemTraits<T>::from_f(u1);
-      up[2] = ElemTraits<T>::from_f(u2);
-      up[3] = ElemTraits<T>::from_f(u3);
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.u) + (size_t)m * d + c) =
+          make_uint2(pack_bf16x2(u0, u1), pack_bf16x2(u2, u3));
     }
     xv[i] = make_float4(u0, u1, u2, u3);  // keep u for the quantiser
   }
@@ -203,9 +240,9 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
     if (c < d) amax = fmaxf(fmaxf(fmaxf(amax, fabsf(xv[i].x)), fmaxf(fabsf(xv[i].y), fabsf(xv[i].z))), fabsf(xv[i].w));
   }
   amax = wave_max(amax);
-  __syncthreads();  // every thread has read red[] for rstd
+  lds_barrier();  // every thread has read red[] for rstd
   if ((t & 63) == 0) red[t >> 6] = amax;
-  __syncthreads();
+  lds_barrier();
   const float r = fmaxf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), 1e-5f);
   const float inv = __fdiv_rn(127.0f, r);
 #pragma unroll
@@ -222,6 +259,18 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
     *reinterpret_cast<uint32_t*>(a.q + (size_t)m * d + c) = packed;
   }
   if (t == 0) a.qr[m] = r;
+}
+
+template <typename T, int MODE>
+hipError_t row_norm_cpt(const RowNormArgs& a, hipStream_t s) {
+  if (a.d <= 1024) hipLaunchKernelGGL((row_norm_kernel<T, MODE, 1>), dim3(a.M), dim3(256), 0, s, a);
+  else if (a.d <= 2048) hipLaunchKernelGGL((row_norm_kernel<T, MODE, 2>), dim3(a.M), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((row_norm_kernel<T, MODE, 4>), dim3(a.M), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+template <typename T>
+hipError_t row_norm_mode(const RowNormArgs& a, hipStream_t s) {
+  return a.mode == 0 ? row_norm_cpt<T, 0>(a, s) : a.mode == 1 ? row_norm_cpt<T, 1>(a, s) : row_norm_cpt<T, 2>(a, s);
 }
 
 __global__ void copy_f32_kernel(float* dst, const float* src, size_t n) {
@@ -384,11 +433,7 @@ hipError_t launch_chunk_start(int et, const CallParams* cp, float* a, float* xs,
 hipError_t launch_row_norm(int et, const RowNormArgs& a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
   if (a.d > 4 * 256 * 4 || a.d % 4 || (a.mode == 1 && a.A > 64)) return hipErrorInvalidValue;
-  if (et == ET_BF16)
-    hipLaunchKernelGGL(row_norm_kernel<bf16_t>, dim3(a.M), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(row_norm_kernel<float>, dim3(a.M), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return et == ET_BF16 ? row_norm_mode<bf16_t>(a, s) : row_norm_mode<float>(a, s);
 }
 
 hipError_t launch_time_embed(int et, const CallParams* cp, void* e, int T, int Tpad, int d, hipStream_t s) {
