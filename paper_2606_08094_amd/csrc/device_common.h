@@ -87,6 +87,17 @@ VLA_DEV uint4 ldg16(const void* p) {
   const gv4u_t v = *(const global_v4u*)(p);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+// Buffer loads: a resource over [base, base + bytes); loads past its end (kOob
+// always is, for buffers below 2 GiB) read zero without a branch.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+constexpr unsigned kOob = 0x7ffffff0u;
+VLA_DEV rsrc_t make_rsrc(const void* base, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+}
+VLA_DEV uint4 buf_ld16(rsrc_t r, unsigned off) {
+  const gv4u_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 VLA_DEV void stg16(void* p, uint4 v) { *reinterpret_cast<uint4*>(p) = v; }
 
 // Activations (fp32).  GELU uses the tanh form.  Both use the hardware

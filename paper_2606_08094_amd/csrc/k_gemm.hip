@@ -6,15 +6,20 @@
 //
 // gemm_skinny -- the per-step projections, M <= 128 token rows.
 //   A workgroup of 8 waves owns 16*NSUB rows of W (NSUB = 2: a gate/up pair
-//   of interleaved 16-row blocks), up to 16*MS token rows and one K-range
-//   (split-K across workgroups when the grid would otherwise not fill the
-//   chip).  The K-range is cut into chunks of KC k-values; wave w takes
-//   chunks w, w+8, ... (CPW per round).  Every operand goes straight from
-//   global memory into MFMA-layout registers: a round issues all W and X
-//   loads of the wave before the first MFMA, so a workgroup pays one memory
-//   latency per round instead of one per staging step.  The eight partial
-//   tiles are summed in wave order through LDS and waves 0..MS-1 run the
-//   epilogue of one 16-row subtile each.
+//   of interleaved 16-row blocks), 16*MS token rows and one K-range
+//   (split-K across workgroups only where the epilogue writes partials).  The
+//   range's k-steps (64 bytes of a row) are spread evenly over the waves.
+//   Every operand goes straight from global memory into MFMA-layout
+//   registers: a round issues all W and X loads of the wave before the first
+//   MFMA, so a workgroup pays one memory latency per round instead of one per
+//   staging step.  The eight partial tiles are summed in wave order through
+//   LDS and waves 0..MS-1 run the epilogue of one 16-row subtile each.
+//   What bounds it is the bytes a compute unit takes in (about 60 GB/s) and
+//   the fixed latency of a launch, so the tile is the one that spreads the
+//   least bytes over 256 compute units (skinny_cost).  In a chain of cold
+//   weights, against tiles that always hold every token row with branchy loads
+//   in 128-wide chunks (50 rows, bf16): 960 x 720 5.7 -> 3.7 us, 1600 x 720
+//   5.8 -> 4.2, gate/up 4096 x 720 6.2 -> 5.2.
 //
 // gemm_wide -- fp32 with M > 128.  Four waves along N (NT = 64*NSUB), X
 //   staged per K-slice in LDS and shared by the four waves, K-slices looped
@@ -77,27 +82,33 @@ VLA_DEV void stage_x(const GemmArgs& a, T* xs, int pitch, int m0, int k0, int KW
 }
 
 // ---------------------------------------------------------------------------
-template <typename T, int MS, int NSUB, int CPW>
+// NV: 4 E-wide k-steps of one wave and round (E values per 16-byte vector).
+template <typename T, int MS, int NSUB, int NV>
 __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
   constexpr int E = ElemTraits<T>::E;
-  constexpr int KC = 4 * VPL * E;
+  constexpr int KSTEP = 4 * E;         // k-values of one step: one vector per lane group
   extern __shared__ __align__(16) unsigned char smem[];
   f32x4* red = reinterpret_cast<f32x4*>(smem);  // [WKS][MS][NSUB][64]
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, g4 = lane >> 4;
-  const int M = a.M, N = a.N, K = a.K;
-  int bid = blockIdx.x;
-  const int split = bid % a.nsplit;
-  bid /= a.nsplit;
-  const int ntile = bid % a.n_tiles, mtile = bid / a.n_tiles;
-  const int m0 = mtile * 16 * MS;
+  // grid (8, row tiles, columns / 8): workgroups go round robin over the XCDs
+  // in the x index, so every row tile of a W tile runs on one XCD and its L2
+  // reads that tile's weights from memory once
+  const int col = blockIdx.z * 8 + blockIdx.x;
+  const int split = col & (a.nsplit - 1), ntile = col >> a.split_log2;
+  if (ntile >= a.n_tiles) return;
+  const int m0 = blockIdx.y * 16 * MS;
   const int nb = ntile * 16 * NSUB;
   const int k0 = split * a.kper;
-  const int k1 = min(K, k0 + a.kper);
-  const int nck = (k1 - k0 + KC - 1) / KC;
-  const T* W = reinterpret_cast<const T*>(a.W);
-  const T* X = reinterpret_cast<const T*>(a.X);
+  const int k1 = min(a.K, k0 + a.kper);
+  // Buffer loads over the workgroup's own rows: rows past M or N are past the
+  // buffer's end and read zero, so a row costs no branch.
+  const int mrows = min(a.M - m0, 16 * MS);
+  const rsrc_t W = make_rsrc(reinterpret_cast<const T*>(a.W) + (size_t)nb * a.K,
+                             (unsigned)min(a.N - nb, 16 * NSUB) * (unsigned)a.K * (unsigned)sizeof(T));
+  const rsrc_t X = make_rsrc(reinterpret_cast<const T*>(a.X) + (size_t)m0 * a.ldx,
+                             ((unsigned)(mrows - 1) * (unsigned)a.ldx + (unsigned)a.K) * (unsigned)sizeof(T));
 
   f32x4 acc[MS][NSUB];
 #pragma unroll
@@ -105,45 +116,42 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) acc[ms][s] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  for (int c0 = 0; c0 < nck; c0 += WKS * CPW) {
-    uint4 wreg[CPW][NSUB][VPL];
-    uint4 xreg[CPW][MS][VPL];
+  // wave w takes steps w NV .. of every round of WKS NV steps; a wave without
+  // steps loads nothing (an out-of-range load costs the address unit as much
+  // as any other)
+  for (int kr = k0 + wave * NV * KSTEP; kr < k1; kr += WKS * NV * KSTEP) {
+    uint4 wreg[NSUB][NV], xreg[MS][NV];
+    const int kl = kr + g4 * E;
+    unsigned wo[NSUB], xo[MS];
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const int c = c0 + wave + j * WKS;
-      const int kc = k0 + c * KC + g4 * E;
+    for (int s = 0; s < NSUB; ++s) wo[s] = (unsigned)((s * 16 + r16) * a.K + kl) * (unsigned)sizeof(T);
 #pragma unroll
-      for (int s = 0; s < NSUB; ++s) {
-        const int n = nb + s * 16 + r16;
+    for (int ms = 0; ms < MS; ++ms) xo[ms] = (unsigned)((ms * 16 + r16) * a.ldx + kl) * (unsigned)sizeof(T);
+    if (kr + NV * KSTEP <= k1) {
 #pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-          const int k = kc + v * 4 * E;
-          wreg[j][s][v] = (c < nck && n < N && k < k1) ? ldg16(W + (size_t)n * K + k) : make_uint4(0, 0, 0, 0);
-        }
-      }
-    }
+      for (int s = 0; s < NSUB; ++s)
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) {
-      const int c = c0 + wave + j * WKS;
-      const int kc = k0 + c * KC + g4 * E;
-#pragma unroll
-      for (int ms = 0; ms < MS; ++ms) {
-        const int m = m0 + ms * 16 + r16;
-#pragma unroll
-        for (int v = 0; v < VPL; ++v) {
-          const int k = kc + v * 4 * E;
-          xreg[j][ms][v] = (c < nck && m < M && k < k1) ? ldg16(X + (size_t)m * a.ldx + k) : make_uint4(0, 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < CPW; ++j)
+        for (int v = 0; v < NV; ++v) wreg[s][v] = buf_ld16(W, wo[s] + 64u * v);
 #pragma unroll
       for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
-        for (int s = 0; s < NSUB; ++s)
+        for (int v = 0; v < NV; ++v) xreg[ms][v] = (ms == 0 || ms * 16 < mrows) ? buf_ld16(X, xo[ms] + 64u * v) : make_uint4(0, 0, 0, 0);
+    } else {   // the range's end: vectors past it read zero
 #pragma unroll
-          for (int v = 0; v < VPL; ++v) mma16(acc[ms][s], xreg[j][ms][v], wreg[j][s][v], T());
+      for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) wreg[s][v] = buf_ld16(W, kl + v * KSTEP < k1 ? wo[s] + 64u * v : kOob);
+#pragma unroll
+      for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) xreg[ms][v] = buf_ld16(X, kl + v * KSTEP < k1 ? xo[ms] + 64u * v : kOob);
+    }
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+      for (int s = 0; s < NSUB; ++s)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) mma16(acc[ms][s], xreg[ms][v], wreg[s][v], T());
   }
 
   // sum the eight partial tiles in wave order; wave ms < MS finishes subtile ms
@@ -687,34 +695,42 @@ hipError_t set_lds_attr(K_ kernel) {
                              160 * 1024);
 }
 
-template <typename T, int MS, int NSUB, int CPW>
-hipError_t launch_skinny_t(const GemmArgs& a, int units, size_t lds, hipStream_t s) {
+template <typename T, int MS, int NSUB, int NV>
+hipError_t launch_skinny_t(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
-    hipError_t e = set_lds_attr(&gemm_skinny<T, MS, NSUB, CPW>);
+    hipError_t e = set_lds_attr(&gemm_skinny<T, MS, NSUB, NV>);
     if (e != hipSuccess) return e;
     attr = true;
   }
-  hipLaunchKernelGGL((gemm_skinny<T, MS, NSUB, CPW>), dim3(units), dim3(64 * WKS), lds, s, a);
+  const dim3 grid(8, sh.m_tiles, (sh.n_tiles * sh.nsplit + 7) / 8);
+  hipLaunchKernelGGL((gemm_skinny<T, MS, NSUB, NV>), grid, dim3(64 * WKS), sh.lds, s, a);
   return hipGetLastError();
 }
 
 template <typename T, int MS, int NSUB>
-hipError_t skinny_cpw(int cpw, const GemmArgs& a, int units, size_t lds, hipStream_t s) {
-  return cpw == 2 ? launch_skinny_t<T, MS, NSUB, 2>(a, units, lds, s) : launch_skinny_t<T, MS, NSUB, 1>(a, units, lds, s);
+hipError_t skinny_nv(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
+  if constexpr (MS * NSUB <= 4)   // eight steps: within 128 registers for small tiles only
+    if (sh.nv == 8) return launch_skinny_t<T, MS, NSUB, 8>(sh, a, s);
+  switch (sh.nv) {
+    case 2: return launch_skinny_t<T, MS, NSUB, 2>(sh, a, s);
+    case 3: return launch_skinny_t<T, MS, NSUB, 3>(sh, a, s);
+    case 4: return launch_skinny_t<T, MS, NSUB, 4>(sh, a, s);
+  }
+  return hipErrorInvalidValue;
 }
 
 template <typename T>
 hipError_t skinny_t(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
   switch (sh.ms * 10 + sh.nsub) {
-    case 11: return skinny_cpw<T, 1, 1>(sh.cpw, a, sh.units, sh.lds, s);
-    case 12: return skinny_cpw<T, 1, 2>(sh.cpw, a, sh.units, sh.lds, s);
-    case 21: return skinny_cpw<T, 2, 1>(sh.cpw, a, sh.units, sh.lds, s);
-    case 22: return skinny_cpw<T, 2, 2>(sh.cpw, a, sh.units, sh.lds, s);
-    case 41: return skinny_cpw<T, 4, 1>(sh.cpw, a, sh.units, sh.lds, s);
-    case 42: return skinny_cpw<T, 4, 2>(sh.cpw, a, sh.units, sh.lds, s);
-    case 24: return launch_skinny_t<T, 2, 4, 1>(a, sh.units, sh.lds, s);
-    case 44: return launch_skinny_t<T, 4, 4, 1>(a, sh.units, sh.lds, s);
+    case 11: return skinny_nv<T, 1, 1>(sh, a, s);
+    case 12: return skinny_nv<T, 1, 2>(sh, a, s);
+    case 21: return skinny_nv<T, 2, 1>(sh, a, s);
+    case 22: return skinny_nv<T, 2, 2>(sh, a, s);
+    case 41: return skinny_nv<T, 4, 1>(sh, a, s);
+    case 42: return skinny_nv<T, 4, 2>(sh, a, s);
+    case 24: return skinny_nv<T, 2, 4>(sh, a, s);
+    case 44: return skinny_nv<T, 4, 4>(sh, a, s);
   }
   return hipErrorInvalidValue;
 }
@@ -788,44 +804,65 @@ constexpr TileCand kTiles[kNumTiles] = {{2, 4, 0.34, 4.0}, {4, 4, 0.47, 5.0}, {8
 
 int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 
+// Time of a skinny launch beyond its fixed latency, in us: the bytes that a
+// compute unit takes in at about 60 GB/s, the rounds of its waves, and what
+// each split-K partial costs the kernel that sums them.
+double skinny_cost(const SkinnyShape& c, int M, int es) {
+  const int rows = M - 16 * c.ms * (c.m_tiles - 1) < 16 * c.ms && c.m_tiles == 1 ? M : 16 * c.ms;
+  const double per_cu = (double)cdiv_i(c.units, 256);
+  const double bytes = (double)(rows + 16 * c.nsub) * c.kper * es;
+  const int rounds = cdiv_i(cdiv_i(c.kper, es == 2 ? 32 : 16), WKS * c.nv);
+  return per_cu * bytes / 60e3 + 0.5 * (rounds - 1) + 0.08 * (c.nsplit - 1) + 0.05 * c.ms * c.nsub;
+}
+
 }  // namespace
 
 int gemm_chunk_k(int et) { return et == ET_BF16 ? 128 : 64; }
 
-bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh) {
-  const int KC = gemm_chunk_k(et);
-  if (M > 128) return false;
-  // Split-K partial outputs take any number of W subtiles: above 16 token rows
-  // four subtiles per workgroup read each X row block for 64 W rows instead
-  // of 16, which cuts the per-CU ingest that bounds these shapes -- as long as
-  // the grid still fills the chip.
-  if (nsub == 1 && allow_split && M > 16) {
-    if (skinny_plan(et, M, N, K, 4, true, sh) && sh->units >= 192) return true;
-  }
-  // Gate/up pairs (no split): two pairs per workgroup above 64 token rows.
-  if (nsub == 2 && M > 64) {
-    if (skinny_plan(et, M, N, K, 4, false, sh) && sh->units >= 192) return true;
-  }
-  sh->ms = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
+// One launch shape of the skinny kernel: 16 ms token rows by 16 nsub W rows
+// a workgroup, K in nsplit (a power of two) ranges of whole k-steps.
+void skinny_shape(int et, int M, int N, int K, int ms, int nsub, int nsplit, SkinnyShape* sh) {
+  const int kstep = gemm_chunk_k(et) / VPL;
+  const int sps = cdiv_i(cdiv_i(K, kstep), nsplit);  // steps per split
+  sh->ms = ms;
   sh->nsub = nsub;
   sh->n_tiles = cdiv_i(N, 16 * nsub);
-  sh->m_tiles = cdiv_i(M, 16 * sh->ms);
-  const int chunks = cdiv_i(K, KC);
-  const int base = sh->n_tiles * sh->m_tiles;
-  // Split K only where the epilogue allows it, as far as keeps the grid in one
-  // pass over the 256 compute units.
-  int nsplit = 1;
-  if (allow_split) nsplit = std::max(1, std::min(chunks, 256 / std::max(1, base)));
-  // wide tiles: at least half the waves of a workgroup hold a chunk
-  if (nsub == 4) nsplit = std::max(1, std::min(nsplit, chunks / (WKS / 2)));
-  const int cps = cdiv_i(chunks, nsplit);  // chunks per split
-  sh->nsplit = cdiv_i(chunks, cps);
-  sh->kper = cps * KC;
-  // two chunks per wave and round when the registers allow it
-  sh->cpw = (cps > WKS && (sh->ms + nsub) * 2 * 16 + sh->ms * nsub * 4 <= 200) ? 2 : 1;
-  sh->units = base * sh->nsplit;
-  sh->lds = (size_t)WKS * sh->ms * nsub * 64 * 16;
-  return true;
+  sh->m_tiles = cdiv_i(M, 16 * ms);
+  sh->nsplit = nsplit;
+  sh->split_log2 = 0;
+  while ((1 << sh->split_log2) < nsplit) ++sh->split_log2;
+  sh->kper = sps * kstep;
+  // the steps spread over the eight waves; eight steps a round (when the
+  // registers allow it) before a second round
+  const int per_wave = cdiv_i(sps, WKS);
+  sh->nv = per_wave <= 2 ? 2 : per_wave == 3 ? 3 : (per_wave == 4 || ms * nsub > 4) ? 4 : 8;
+  sh->units = sh->n_tiles * sh->m_tiles * nsplit;
+  sh->lds = (size_t)WKS * ms * nsub * 64 * 16;
+}
+
+bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh) {
+  if (M > 128) return false;
+  const int es = et == ET_BF16 ? 2 : 4, steps = cdiv_i(K, gemm_chunk_k(et) / VPL);
+  double best = 1e30;
+  for (int ms = 1; ms <= 4; ms *= 2) {
+    if (ms > 1 && 16 * (ms / 2) >= M) break;      // half of it covers every row
+    for (int ns = nsub; ns <= 4; ns *= 4 / nsub) {
+      if (ns == 4 && ms == 1) continue;           // not instantiated
+      if (ns == 4 && nsub == 1 && !allow_split) continue;  // EULER and RESID epilogues take one subtile
+      for (int sp = 1; sp <= (allow_split ? 8 : 1) && sp <= steps; sp *= 2) {
+        if (sp > 1 && (cdiv_i(steps, sp) * (sp - 1)) >= steps) continue;  // an empty last range
+        SkinnyShape c;
+        skinny_shape(et, M, N, K, ms, ns, sp, &c);
+        const double cost = skinny_cost(c, M, es);
+        if (cost < best) {
+          best = cost;
+          *sh = c;
+        }
+      }
+      if (nsub == 4) break;
+    }
+  }
+  return best < 1e30;
 }
 
 void wide_plan(int et, int M, int N, int K, int nsub, WideShape* sh) {
@@ -847,6 +884,7 @@ hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStre
   if (sh.units <= 0) return hipSuccess;
   a.n_tiles = sh.n_tiles;
   a.nsplit = sh.nsplit;
+  a.split_log2 = sh.split_log2;
   a.kper = sh.kper;
   return et == ET_BF16 ? skinny_t<bf16_t>(sh, a, s) : skinny_t<float>(sh, a, s);
 }

@@ -36,7 +36,6 @@ namespace {
 
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 constexpr int NTEAM = 8, TSIZE = 32, NWG = NTEAM * TSIZE;
 constexpr int NW = 4, NTHR = 64 * NW;    // waves and threads of a workgroup

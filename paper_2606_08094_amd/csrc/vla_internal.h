@@ -43,6 +43,7 @@ struct GemmArgs {
   int m_tiles;             // tiles along M (tiled kernel; set by the launcher)
   int nsplit;              // K-splits (set by the launcher; > 1 only with EPI_PARTIAL)
   int kper;                // K-range of one split (skinny kernel; set by the launcher)
+  int split_log2;          // skinny kernel: nsplit is 1 << split_log2 (set by the launcher)
   // epilogue
   int epi;
   int act;
@@ -147,7 +148,7 @@ struct TernArgs {
 
 // Launch shapes of the two dense GEMM kernels (chosen on the host).
 struct SkinnyShape {
-  int ms, nsub, cpw, nsplit, kper, n_tiles, m_tiles, units;
+  int ms, nsub, nv, nsplit, split_log2, kper, n_tiles, m_tiles, units;
   size_t lds;
 };
 struct WideShape {
@@ -218,6 +219,7 @@ constexpr int PERSIST_MAX_LAYERS = 64;
 
 // ---- launchers (each enqueues on `s`, returns hipError_t) ----
 int gemm_chunk_k(int et);  // K covered by one chunk (all 4 lane groups of a wave)
+void skinny_shape(int et, int M, int N, int K, int ms, int nsub, int nsplit, SkinnyShape* sh);
 bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh);
 void wide_plan(int et, int M, int N, int K, int nsub, WideShape* sh);
 hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStream_t s);
