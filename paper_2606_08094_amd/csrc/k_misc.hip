@@ -206,13 +206,21 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
       ss += xv[i].x * xv[i].x + xv[i].y * xv[i].y + xv[i].z * xv[i].z + xv[i].w * xv[i].w;
     }
   }
-  ss = wave_sum_dpp(ss);
+  ss = a.exact ? wave_sum(ss) : wave_sum_dpp(ss);
   if ((t & 63) == 0) red[t >> 6] = ss;
   lds_barrier();   // LDS only: the stores of x complete behind the rest
-  const float ms = (red[0] + red[1] + red[2] + red[3]) * inv_d + a.eps;
-  // 1 / sqrt(ms): the hardware estimate (1 ulp) and one Newton step
-  float rstd = __builtin_amdgcn_rsqf(ms);
-  rstd = rstd + 0.5f * rstd * (1.0f - ms * rstd * rstd);
+  const float rows = red[0] + red[1] + red[2] + red[3];
+  float rstd;
+  if (a.exact) {
+    // W2A8 models: correctly rounded steps, so that the int8 codes of u, and
+    // all that follows from them, do not hang on the hardware's estimate
+    rstd = 1.0f / sqrtf(rows / (float)d + a.eps);
+  } else {
+    // the hardware estimate (1 ulp) and one Newton step
+    const float ms = rows * inv_d + a.eps;
+    rstd = __builtin_amdgcn_rsqf(ms);
+    rstd = rstd + 0.5f * rstd * (1.0f - ms * rstd * rstd);
+  }
 #pragma unroll
   for (int i = 0; i < CPT; ++i) {
     const int c = 4 * (t + 256 * i);

@@ -687,7 +687,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
     };
     RowNormArgs rn{};
     rn.mode = 1; rn.M = M; rn.d = d; rn.x = p->x; rn.a = p->a; rn.W_in = m->W_in; rn.xs = p->xs;
-    rn.E_pos = m->E_pos; rn.n = nt; rn.stok = stok; rn.b_in = m->b_in; rn.A = A; rn.eps = c.rms_eps; rn.u = p->u; rn.u_f32 = u32;
+    rn.E_pos = m->E_pos; rn.n = nt; rn.stok = stok; rn.b_in = m->b_in; rn.A = A; rn.eps = c.rms_eps; rn.exact = m->tern; rn.u = p->u; rn.u_f32 = u32;
     if (L > 0) {
       rn.gamma = modk;
       rn.beta = modk + d;
@@ -707,7 +707,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
         const SubW& sw = subs[j];
         const float* alp = modk + ((size_t)l * ns + j) * 3 * d + 2 * d;
         RowNormArgs nr{};
-        nr.mode = 0; nr.M = M; nr.d = d; nr.x = p->x; nr.eps = c.rms_eps; nr.u = p->u; nr.u_f32 = u32;
+        nr.mode = 0; nr.M = M; nr.d = d; nr.x = p->x; nr.eps = c.rms_eps; nr.exact = m->tern; nr.u = p->u; nr.u_f32 = u32;
         next_gb(l, j, &nr.gamma, &nr.beta);
         // the head projection is dense: it reads u in the element type
         const bool last_sub = l == L - 1 && j == (int)subs.size() - 1;
@@ -2003,7 +2003,7 @@ vla_status build_prefill_plan(vla_backbone* bb, PrefillPlan* p) {
 
   {  // the residual stream starts as the input rows; first norm
     RowNormArgs r{};
-    r.mode = 2; r.M = M; r.d = d; r.x = p->x; r.gamma = gam(0, 0); r.beta = gam(0, 0) + d; r.eps = bc.rms_eps;
+    r.mode = 2; r.M = M; r.d = d; r.x = p->x; r.gamma = gam(0, 0); r.beta = gam(0, 0) + d; r.eps = bc.rms_eps; r.exact = tern;
     r.u = p->u; r.u_f32 = tern ? 1 : 0;
     if (tern) {
       r.q = p->q8;
@@ -2113,7 +2113,7 @@ vla_status build_prefill_plan(vla_backbone* bb, PrefillPlan* p) {
     a.scale = 1.0f / std::sqrt((float)hd);
     bld.attn(a);
     RowNormArgs nr{};
-    nr.mode = 0; nr.M = M; nr.d = d; nr.x = p->x; nr.eps = bc.rms_eps; nr.u = p->u; nr.u_f32 = tern ? 1 : 0;
+    nr.mode = 0; nr.M = M; nr.d = d; nr.x = p->x; nr.eps = bc.rms_eps; nr.exact = tern; nr.u = p->u; nr.u_f32 = tern ? 1 : 0;
     nr.gamma = gam(l, 1);
     nr.beta = gam(l, 1) + d;
     if (tern) {
@@ -2132,7 +2132,7 @@ vla_status build_prefill_plan(vla_backbone* bb, PrefillPlan* p) {
     // ---- MLP sublayer
     const bool last = l == L - 1;
     RowNormArgs nm{};
-    nm.mode = 0; nm.M = M; nm.d = d; nm.x = p->x; nm.eps = bc.rms_eps;
+    nm.mode = 0; nm.M = M; nm.d = d; nm.x = p->x; nm.eps = bc.rms_eps; nm.exact = tern;
     if (!last) {
       nm.gamma = gam(l + 1, 0);
       nm.beta = gam(l + 1, 0) + d;

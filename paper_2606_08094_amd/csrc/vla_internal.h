@@ -126,6 +126,7 @@ struct RowNormArgs {
   const float* gamma;
   const float* beta;
   float eps;
+  int exact;               // 1 (W2A8 models): 1 / sqrt by correctly rounded steps
   void* u;                 // [M][d] element type (u_f32 = 0) or fp32
   int u_f32;
   int8_t* q;               // if set (u_f32 = 1): also the int8 absmax quantisation of u, [M][d]
