@@ -159,7 +159,9 @@ vla_status vla_prefix_kv_build_noalloc(vla_model* model, const void* prefix_hidd
  * It is reported, once, as VLA_E_DEVICE by the first vla_denoise (before it
  * enqueues anything) or vla_model_check on the same model that runs after the
  * failed call has completed.  Each launch starts with a cleared record, so
- * one failure does not affect later calls.
+ * one failure does not affect later calls.  The persistent kernel takes every
+ * compute unit at once; where several models of a process use it, its launches
+ * on one device run one after another, whatever their streams.
  */
 vla_status vla_denoise(vla_model* model, const void* kv_cache, size_t kv_cache_bytes, int32_t batch,
                        int32_t prefix_len, const float* noise, const float* state,
@@ -190,8 +192,7 @@ vla_status vla_ternary_gemm(const int8_t* x, const uint8_t* w_packed, int32_t M,
  *    replayed, 2 (default) = one persistent kernel (every workgroup resident
  *    at once) for the whole step loop where the model and device support it
  *    (batch 1, bf16, joint attention,
- *    H % 8 == 0, the shape limits of the team layout, none of the causal,
- *    RoPE or state-token variants), else as 1.
+ *    H % 8 == 0, the shape limits of the team layout), else as 1.
  *  VLA_OPT_PROFILE: R in 1..1000 = time every launch of the following
  *    vla_denoise calls with HIP events (launch-per-phase driver; read with
  *    vla_profile_read).  Each launch runs R times back to back between its
@@ -211,24 +212,21 @@ vla_status vla_ternary_gemm(const int8_t* x, const uint8_t* w_packed, int32_t M,
  *    use a causal one): 1 = action token i attends only to action tokens
  *    0 .. i in self and joint attention, every prefix row stays visible;
  *    0 (default) = bidirectional.  Set it before the first vla_denoise that
- *    should use it; changing it discards the cached plans.  Causal models
- *    run on loop modes 0 and 1 (the persistent kernel is unmasked).
+ *    should use it; changing it discards the cached plans.
  *  VLA_OPT_ROPE_BASE: architecture variant (the paper's expert has no
  *    positions beyond the learned E_pos): value = base > 1 of a rotary
  *    position embedding (rotate-half form) on the queries and keys of self
  *    and joint attention; 0 (default) = none.  Action token i sits at
  *    position i in self attention and P + i in joint attention, whose cached
  *    prefix keys vla_prefix_kv_build rotates to positions 0 .. P-1 (build
- *    the cache after setting it).  Discards the cached plans; such models run
- *    on loop modes 0 and 1.
+ *    the cache after setting it).  Discards the cached plans.
  *  VLA_OPT_STATE_TOKEN: architecture variant of the input embedding (the
  *    paper adds the projected state to every action token; pi0-style experts
  *    give it a token of its own): 1 = each request runs n + 1 token rows, row
  *    0 = s W_s^T + b_s and row 1 + i = a_i W_in^T + b_in + E_pos[i]; the
  *    state row takes part in attention (and is token 0 for the causal mask and
  *    RoPE) but yields no action, so actions_out keeps its [B, n, d_action]
- *    layout.  0 (default) = the paper's embedding.  Discards the cached plans;
- *    such models run on loop modes 0 and 1.
+ *    layout.  0 (default) = the paper's embedding.  Discards the cached plans.
  *  VLA_OPT_PERSIST_SPIN_LIMIT: polls of one barrier wait of the persistent
  *    step kernel before it gives up (value >= 0; -1 = the default, 2^20
  *    polls, about 0.25 s).  For tests of the failure path: a small value makes waits time

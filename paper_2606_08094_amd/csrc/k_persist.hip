@@ -118,12 +118,18 @@ VLA_DEV void arrive(Sync& s, int team, int rank, bool drain = true) {
   if (drain) __builtin_amdgcn_s_waitcnt(0);  // this thread's stores have completed
   __syncthreads();
   ++s.bk;
-  if (GRID) {
-    if (threadIdx.x < NTEAM)   // one copy per thread
-      __hip_atomic_store(s.flag + threadIdx.x * PERSIST_GFLAG_STRIDE + team * 32 + rank, s.bk, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-  } else if (threadIdx.x == 0) {
-    __builtin_amdgcn_raw_buffer_store_b32(s.bk, mkr(s.tflag, (size_t)NWG * 4), (team * 32 + rank) * 4, 0, 0);
+  // The first wave as a whole stores, lanes without a copy past the buffer's
+  // end: a branch of single lanes here has cost values that live through the
+  // loop in the other lanes' registers (the compiler placed copies inside it).
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
+    const int lane = threadIdx.x;
+    if (GRID)   // one copy per lane
+      __builtin_amdgcn_raw_buffer_store_b32(s.bk, mkr(s.flag, (size_t)PERSIST_SYNC_WORDS * 4),
+                                            lane < NTEAM ? (lane * PERSIST_GFLAG_STRIDE + team * 32 + rank) * 4 : (int)kOob,
+                                            0, SC1);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(s.bk, mkr(s.tflag, (size_t)NWG * 4),
+                                            lane == 0 ? (team * 32 + rank) * 4 : (int)kOob, 0, 0);
   }
 }
 
@@ -146,7 +152,7 @@ VLA_DEV unsigned flag_peek(const Sync& s, int team) {
 // Returns false (in every thread) if the run must stop.
 template <bool GRID>
 VLA_DEV bool wait_flags(Sync& s, int team, int* lds_flag, unsigned peek) {
-  if (threadIdx.x < 64) {
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0) {
     const unsigned target = s.bk;
     bool ok = true;
     if (!__all(peek >= target)) {
@@ -168,7 +174,7 @@ VLA_DEV bool wait_flags(Sync& s, int team, int* lds_flag, unsigned peek) {
         }
       }
     }
-    if (threadIdx.x == 0) *lds_flag = ok ? 1 : 0;
+    *lds_flag = ok ? 1 : 0;   // one value from every lane
   }
   __syncthreads();
   return *lds_flag != 0;
@@ -368,7 +374,13 @@ size_t lds_main(int hd) {
 }
 
 // FOLD: the chunk has at most 50 rows (see tile_mma).
-template <int HD, int DPT, bool FOLD>
+// VAR: the architecture variants (causal action tokens, RoPE, a state token of
+// its own), each switched by an argument.  A form of its own, so that the
+// plain expert's kernel, which uses nearly every register, carries none of it;
+// always unfolded (the pi0-shaped state token makes 51 rows).  A pi0-shaped
+// chunk with all three over 571 prefix rows: 6.26 ms, against 10.5 ms as
+// about 1640 launches of a graph.
+template <int HD, int DPT, bool FOLD, bool VAR>
 __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   using L = PLds<HD>;
   constexpr int VPR = HD / 8;              // 16-byte vectors per K/V row
@@ -380,9 +392,12 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int flag;
   __shared__ float red_s[2][NW];
-  __shared__ float sa[2][32];              // a of this workgroup's rows (broadcast copy)
+  __shared__ float sa[2][32];              // a of this workgroup's rows
   __shared__ float hv[2][NW][32];          // head partial sums per wave
   __shared__ PLayer lt[PERSIST_MAX_LAYERS];
+  // RoPE: (cos, sin) of the lane's four rows at its column pair's angle, the
+  // same in every layer and step
+  __shared__ float2 rot_s[VAR ? 4 : 1][VAR ? NTHR : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g4 = lane >> 4;
@@ -403,6 +418,8 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   if (s_rank >= TSIZE) return;
   const int team = s_team, rank = s_rank;
   const int n = a.n, d = a.d, HT = a.HT, A = a.A;
+  const int st = VAR ? a.stok : 0;         // 1: token row 0 is the state token, row t + 1 action t
+  const bool rot = VAR && a.rot != nullptr;
   const int HTD = HT * HD, QW = (HT + 2) * HD, F8 = a.F / 8, S = a.nsplit;
   const int QT = (n + 15) / 16;
   const int dq = a.H * HD, dkv = a.G * HD;
@@ -418,12 +435,12 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   const int tcap = a.trace_all ? PERSIST_TRACE_WG : PERSIST_TRACE_MAX;
   int tev = 0;
   auto mark = [&]() {
-    if (trace && tid == 0 && tev < tcap) trace[tev] = __builtin_amdgcn_s_memrealtime();
+    if (trace && wave == 0 && tev < tcap) trace[tev] = __builtin_amdgcn_s_memrealtime();   // one value from every lane
     ++tev;
   };
   // A barrier timed out: leave, marking the chunk as failed (NaN).
   auto bail = [&]() {
-    for (int i = tid; i < n * a.A; i += NTHR) a.cp->actions_out[i] = __int_as_float(0x7fc00000);
+    for (int i = tid; i < (n - st) * a.A; i += NTHR) a.cp->actions_out[i] = __int_as_float(0x7fc00000);
   };
 
   // team-local workspace
@@ -441,9 +458,14 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   const int mrow[2] = {rank, rank + TSIZE};
   const bool mok[2] = {rank < n, rank + TSIZE < n};
   float xr[2][DPT];
-  float areg[2] = {0.f, 0.f};              // thread j < A: a[mrow][j]
-  for (int r = 0; r < 2; ++r)
-    if (mok[r] && tid < A) areg[r] = a.a0[(size_t)mrow[r] * A + tid];
+  // a of the workgroup's two rows (thread j < 32 owns column j; zero past A and
+  // in the state row).  In LDS and not in a register of the first threads: a
+  // value that lives through the whole loop in a few lanes was lost there in
+  // some forms of this kernel (the compiler copied its register inside
+  // a one-lane branch, so only that lane kept it).
+  if (tid < 32)
+    for (int r = 0; r < 2; ++r)
+      sa[r][tid] = mok[r] && mrow[r] >= st && tid < A ? a.a0[(size_t)(mrow[r] - st) * A + tid] : 0.f;
 
   const size_t modstep = (size_t)a.L * 2 * 3 * d;
   auto gam = [&](int k, int l, int j) { return a.mods + k * modstep + ((size_t)l * 2 + j) * 3 * d; };
@@ -549,22 +571,25 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   // x = a W_in^T + xs + E_pos (input embedding of the chunk tokens).  W_in is
   // the zero-padded [d][32] copy; sa holds a with zeros past A.
   const rsrc_t WIr = mkr(a.w_in, (size_t)d * 32 * 2);
-  const rsrc_t EPr = mkr(a.e_pos, (size_t)n * d * 2);
+  const rsrc_t EPr = mkr(a.e_pos, (size_t)(n - st) * d * 2);
   const rsrc_t WOr = mkr(a.w_out, (size_t)A * d * 2);
   auto embed = [&]() {
-    if (tid < 32) {
-      sa[0][tid] = tid < A ? areg[0] : 0.f;
-      sa[1][tid] = tid < A ? areg[1] : 0.f;
-    }
     uint4 wv[DPT][4];
 #pragma unroll
     for (int e = 0; e < DPT; ++e)
 #pragma unroll
       for (int q = 0; q < 4; ++q) wv[e][q] = ld16<0>(WIr, (unsigned)((c0 + e) * 32 + 8 * q) * 2u);
-    float base[DPT], ep[2][DPT];
-    ldf(base, a.xs + c0);
+    // state token: row 0 is xs alone (its a is zero and its E_pos reads zero),
+    // the action rows start from b_in
+    float base[2][DPT], ep[2][DPT];
+    if constexpr (VAR) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) ldbf(ep[r], EPr, mok[r] ? (unsigned)(mrow[r] * d + c0) * 2u : OOB);
+      for (int r = 0; r < 2; ++r) ldf(base[r], (mrow[r] < st || !st ? a.xs : a.b_in) + c0);
+    } else {
+      ldf(base[0], a.xs + c0);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) ldbf(ep[r], EPr, mok[r] && mrow[r] >= st ? (unsigned)((mrow[r] - st) * d + c0) * 2u : OOB);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < DPT; ++e) {
@@ -573,7 +598,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       for (int q = 0; q < 4; ++q) unpack16(wv[e][q], f + 8 * q, bf16_t());
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
-        float v = base[e] + ep[r][e];
+        float v = base[VAR ? r : 0][e] + ep[r][e];
 #pragma unroll
         for (int t = 0; t < 32; ++t) v += sa[r][t] * f[t];
         xr[r][e] = mok[r] ? v : 0.f;
@@ -629,16 +654,13 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         float v = a.b_out[tid];
 #pragma unroll
         for (int w = 0; w < NW; ++w) v += hv[r][w][tid];
-        areg[r] += dt * v;
-      }
-      if (k == a.T - 1 && team == 0) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          if (!mok[r]) continue;
-          float o = areg[r];
+        const float an = sa[r][tid] + dt * v;
+        if (mrow[r] >= st) sa[r][tid] = an;   // the state token's a stays zero
+        if (k == a.T - 1 && team == 0 && mok[r] && mrow[r] >= st) {
+          float o = an;
           if (cp->act_std) o *= cp->act_std[tid];
           if (cp->act_mean) o += cp->act_mean[tid];
-          cp->actions_out[(size_t)mrow[r] * A + tid] = o;
+          cp->actions_out[(size_t)(mrow[r] - st) * A + tid] = o;
         }
       }
     }
@@ -650,7 +672,15 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   auto qkv_rows = [&](int (&wrow)[2], int (&ocol)[2]) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      const int t = rank + TSIZE * s;
+      int t = rank + TSIZE * s;
+      if (rot) {
+        // RoPE: a rank with q or k columns holds both tiles of a rotation pair
+        // (columns c and c + hd / 2 of a head), the others one v tile each
+        constexpr int PH = HD / 32;          // tile pairs per head
+        const int np = (HT + 1) * PH;        // pairs of the team's q and k heads
+        if (rank < np) t = (rank / PH) * 2 * PH + rank % PH + PH * s;
+        else t = s == 0 ? 2 * np + (rank - np) : NTQ;
+      }
       wrow[s] = -1;
       ocol[s] = -1;
       if (t >= NTQ) continue;
@@ -679,6 +709,18 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
     wrow[0] = rank * DCOL;
     wrow[1] = DCOL > 16 ? rank * DCOL + 16 : -1;
   };
+
+  if constexpr (VAR) {
+    if (rot) {
+      constexpr int PH = HD / 32;
+      const int i = (rank % PH) * 16 + r16;
+      for (int q = 0; q < 4; ++q) {
+        const int m = 16 * wave + 4 * g4 + q;
+        rot_s[q][tid] = (rank < (HT + 1) * PH && m < n) ? reinterpret_cast<const float2*>(a.rot)[m * (HD / 2) + i]
+                                                         : make_float2(1.0f, 0.0f);
+      }
+    }
+  }
 
   // attention split of this rank
   const int npre = a.P, nself = n;
@@ -776,6 +818,17 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         tile_mma<2, DPT / 2, FOLD>(acc, wq, ubase, (unsigned)(n * d * 2), d, n, smem);
         __syncthreads();
         tile_reduce<2>(acc, red);
+        if constexpr (VAR) {
+          if (rot && rank < (HT + 1) * (HD / 32)) {   // the pair's rotation, on the fp32 sums
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float2 cs = rot_s[i][tid];
+              const float lo = acc[0][0][i], hi = acc[0][1][i];
+              acc[0][0][i] = lo * cs.x - hi * cs.y;
+              acc[0][1][i] = hi * cs.x + lo * cs.y;
+            }
+          }
+        }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
           if (oc[s] < 0) continue;
@@ -849,6 +902,8 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
           for (int jb = 0; jb < KBA_MAX; ++jb) {
             const int j = jbeg + jb;
             const int cnt = jb >= nblk ? 0 : j < nbp ? min(32, npre - j * 32) : min(32, nself - (j - nbp) * 32);
+            // causal: action key (j - nbp) * 32 + kr is visible to query qrow when it is <= qrow
+            const int lim = (VAR && a.causal && j >= nbp) ? min(cnt, qrow - (j - nbp) * 32 + 1) : cnt;
             const bf16_t* kl = reinterpret_cast<const bf16_t*>(smem + jb * L::BUF);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -868,13 +923,15 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
                 const int kr = 8 * g4 + 4 * t + i;
-                sv[jb][t][i] = (kr < cnt) ? sv[jb][t][i] * sc : -INFINITY;
+                sv[jb][t][i] = (kr < lim) ? sv[jb][t][i] * sc : -INFINITY;
                 mrun = fmaxf(mrun, sv[jb][t][i]);
               }
             }
           }
           mrun = fmaxf(mrun, __shfl_xor(mrun, 16, 64));
           mrun = fmaxf(mrun, __shfl_xor(mrun, 32, 64));
+          // a query with no visible key in the split keeps weight 0
+          const float mref = VAR && mrun == -INFINITY ? 0.0f : mrun;
           float lrun = 0.0f;
 #pragma unroll
           for (int jb = 0; jb < KBA_MAX; ++jb) {
@@ -885,7 +942,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
             for (int t = 0; t < 2; ++t)
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
-                p[4 * t + i] = exp2f(sv[jb][t][i] - mrun);
+                p[4 * t + i] = exp2f(sv[jb][t][i] - mref);
                 lrun += p[4 * t + i];
               }
             uint4 pb;
@@ -1234,33 +1291,35 @@ size_t persist_lds_bytes(int hd, int HT) {
 }
 
 namespace {
-template <bool FOLD>
+template <bool FOLD, bool VAR>
 const void* persist_fn_t(int hd, int dpt) {
   switch (hd * 10 + dpt) {
-    case 2564: return reinterpret_cast<const void*>(&persist_kernel<256, 4, FOLD>);
-    case 2562: return reinterpret_cast<const void*>(&persist_kernel<256, 2, FOLD>);
-    case 1284: return reinterpret_cast<const void*>(&persist_kernel<128, 4, FOLD>);
-    case 1282: return reinterpret_cast<const void*>(&persist_kernel<128, 2, FOLD>);
-    case 644: return reinterpret_cast<const void*>(&persist_kernel<64, 4, FOLD>);
-    case 642: return reinterpret_cast<const void*>(&persist_kernel<64, 2, FOLD>);
+    case 2564: return reinterpret_cast<const void*>(&persist_kernel<256, 4, FOLD, VAR>);
+    case 2562: return reinterpret_cast<const void*>(&persist_kernel<256, 2, FOLD, VAR>);
+    case 1284: return reinterpret_cast<const void*>(&persist_kernel<128, 4, FOLD, VAR>);
+    case 1282: return reinterpret_cast<const void*>(&persist_kernel<128, 2, FOLD, VAR>);
+    case 644: return reinterpret_cast<const void*>(&persist_kernel<64, 4, FOLD, VAR>);
+    case 642: return reinterpret_cast<const void*>(&persist_kernel<64, 2, FOLD, VAR>);
     default: return nullptr;
   }
 }
-// chunks of at most 50 rows take the folded-tail form of the GEMM phases
-const void* persist_fn(int hd, int d, int n) {
-  return n <= 50 ? persist_fn_t<true>(hd, d / NTHR) : persist_fn_t<false>(hd, d / NTHR);
+// plain chunks of at most 50 rows take the folded-tail form of the GEMM phases
+const void* persist_fn(int hd, int d, int n, bool var) {
+  const int dpt = d / NTHR;
+  if (var) return persist_fn_t<false, true>(hd, dpt);
+  return n <= 50 ? persist_fn_t<true, false>(hd, dpt) : persist_fn_t<false, false>(hd, dpt);
 }
 }  // namespace
 
 bool persist_resident(int d, int hd, int HT) {
-  const void* fns[2] = {persist_fn(hd, d, 1), persist_fn(hd, d, 64)};
-  if (!fns[0] || !fns[1]) return false;
+  const void* fns[3] = {persist_fn(hd, d, 1, false), persist_fn(hd, d, 64, false), persist_fn(hd, d, 1, true)};
   int dev = 0, cus = 0, nb = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus != NWG)
     return false;
   const size_t lds = persist_lds_bytes(hd, HT);
   for (const void* fn : fns) {
+    if (!fn) return false;
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return false;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, NTHR, lds) != hipSuccess || nb < 1) return false;
   }
@@ -1274,7 +1333,7 @@ bool persist_resident(int d, int hd, int HT) {
 hipError_t launch_persist(const PersistArgs& a, hipStream_t s) {
   const size_t lds = persist_lds_bytes(a.hd, a.HT);
   void* args[] = {const_cast<PersistArgs*>(&a)};
-  const void* fn = persist_fn(a.hd, a.d, a.n);
+  const void* fn = persist_fn(a.hd, a.d, a.n, a.causal || a.stok || a.rot != nullptr);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

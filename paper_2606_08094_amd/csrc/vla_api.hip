@@ -149,6 +149,7 @@ struct vla_model {
   int attn_splits = 0;            // key splits of the launch-per-phase attention (0 = automatic)
   long spin_limit = PERSIST_SPIN_DEFAULT;  // persistent kernel: polls of a barrier wait (VLA_OPT_PERSIST_SPIN_LIMIT)
   int persist_dev_ok = -1;        // the device holds the persistent kernel's whole grid (-1 = not yet asked)
+  bool persist_counted = false;   // counted by the persistent launches' gate
   void* last_profiled = nullptr;  // Plan* of the last profiled call
   void* last_traced = nullptr;    // Plan* of the last traced call
   hipStream_t cap_stream = nullptr;
@@ -416,16 +417,54 @@ int mlp_act(int mlp) {
 }
 
 // The persistent step kernel covers the batch-1 bf16 dense expert with joint
+// The persistent kernel needs every compute unit at once, so two of them must
+// not be dispatched side by side (two models on two streams): each would hold
+// part of the device and wait for the rest.  As soon as a second live model
+// has a persistent plan, every launch on a device waits (on the device, by an
+// event) for the previous one there.  A model's first persistent plan is
+// counted before the device synchronisation that ends its build, so launches
+// made earlier, without an event, have completed by then.
+struct PersistGate {
+  static constexpr int kDevices = 64;
+  std::mutex mx;
+  int models = 0;
+  hipEvent_t last[kDevices] = {};
+  hipError_t launch(const PersistArgs& a, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(mx);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    hipError_t e;
+    if (models < 2) return launch_persist(a, s);
+    const bool known = hipStreamIsCapturing(s, &cap) == hipSuccess && hipGetDevice(&dev) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    // a captured launch cannot wait for an event recorded outside its capture
+    if (!known || cap != hipStreamCaptureStatusNone || dev >= kDevices) return launch_persist(a, s);
+    if (!last[dev]) {
+      if ((e = hipEventCreateWithFlags(&last[dev], hipEventDisableTiming)) != hipSuccess) return e;
+    } else if ((e = hipStreamWaitEvent(s, last[dev], 0)) != hipSuccess) {
+      return e;
+    }
+    if ((e = launch_persist(a, s)) != hipSuccess) return e;
+    return hipEventRecord(last[dev], s);
+  }
+  void add(int n) {
+    std::lock_guard<std::mutex> lk(mx);
+    models += n;
+  }
+};
+PersistGate& persist_gate() {
+  static PersistGate* g = new PersistGate();   // outlives every model
+  return *g;
+}
+
 // attention whose shape fits its team layout (see persist_supported).
 bool persist_eligible(vla_model* m, int B, int P, int T) {
-  // its attention is unmasked and unrotated, its rows are the action tokens alone
-  if (m->causal || m->rope_base > 0.0f || m->state_token) return false;
   const vla_config& c = m->cfg;
   int kba = 0, nsplit = 0;
   const bool shape_ok = !m->tern && m->et == ET_BF16 && c.pattern == VLA_PAT_JOINT && !c.head_regression &&
                         B == 1 && T >= 1 && c.n_layers >= 1 && c.n_layers <= PERSIST_MAX_LAYERS &&
-                        persist_supported(m->d, c.head_dim, c.n_heads, c.n_kv_heads, c.d_ff, c.n_action, P,
-                                          c.d_action, c.mlp != VLA_MLP_GELU, &kba, &nsplit);
+                        persist_supported(m->d, c.head_dim, c.n_heads, c.n_kv_heads, c.d_ff,
+                                          c.n_action + (m->state_token ? 1 : 0), P, c.d_action, c.mlp != VLA_MLP_GELU, &kba, &nsplit);
   if (!shape_ok) return false;
   if (m->persist_dev_ok < 0) m->persist_dev_ok = persist_resident(m->d, c.head_dim, c.n_heads / 8) ? 1 : 0;
   return m->persist_dev_ok == 1;
@@ -524,12 +563,16 @@ vla_status build_plan(vla_model* m, Plan* p) {
 
   if (p->persist) {
     PersistArgs pa{};
-    pa.L = L; pa.d = d; pa.H = c.n_heads; pa.G = c.n_kv_heads; pa.hd = hd; pa.F = F; pa.n = n; pa.P = P;
+    if (!m->persist_counted) {
+      persist_gate().add(1);
+      m->persist_counted = true;
+    }
+    pa.L = L; pa.d = d; pa.H = c.n_heads; pa.G = c.n_kv_heads; pa.hd = hd; pa.F = F; pa.n = nt; pa.P = P;
     pa.A = A; pa.T = T;
     pa.glu = c.mlp != VLA_MLP_GELU;
     pa.act = mlp_act(c.mlp);
     pa.HT = c.n_heads / 8;
-    if (!persist_supported(d, hd, c.n_heads, c.n_kv_heads, F, n, P, A, pa.glu, &pa.kba, &pa.nsplit))
+    if (!persist_supported(d, hd, c.n_heads, c.n_kv_heads, F, nt, P, A, pa.glu, &pa.kba, &pa.nsplit))
       return fail(VLA_E_UNSUPPORTED, "persistent kernel: unsupported shape");
     pa.eps = c.rms_eps;
     pa.scale = 1.0f / std::sqrt((float)hd);
@@ -583,13 +626,30 @@ vla_status build_plan(vla_model* m, Plan* p) {
     pa.b_out = m->b_out;
     pa.a0 = p->a;
     const int HT = pa.HT;
-    VLA_TRY(al(&pa.u, (size_t)8 * n * d * 2));
-    VLA_TRY(al(&pa.qkv, (size_t)8 * n * (HT + 2) * hd * 2));
-    VLA_TRY(al(&pa.apart, (size_t)8 * pa.nsplit * n * HT * hd * 2));
-    VLA_TRY(al((void**)&pa.astat, (size_t)8 * pa.nsplit * n * HT * 2 * 4));
-    VLA_TRY(al(&pa.omerged, (size_t)8 * n * HT * hd * 2));
-    VLA_TRY(al(&pa.hbuf, (size_t)8 * n * (F / 8) * 2));
-    VLA_TRY(al((void**)&pa.delta, (size_t)2 * 8 * n * d * 4));
+    pa.causal = m->causal;
+    pa.stok = m->state_token;
+    pa.b_in = m->b_in;
+    if (m->rope_base > 0.0f) {
+      // token row t at position P + i, i = t: the angles of every row and pair, once per plan
+      std::vector<float> cs((size_t)nt * hd);
+      for (int t = 0; t < nt; ++t)
+        for (int i = 0; i < hd / 2; ++i) {
+          const double w = std::pow((double)m->rope_base, -2.0 * i / hd);
+          cs[((size_t)t * (hd / 2) + i) * 2] = (float)std::cos((P + t) * w);
+          cs[((size_t)t * (hd / 2) + i) * 2 + 1] = (float)std::sin((P + t) * w);
+        }
+      float* dcs = nullptr;
+      VLA_TRY(al((void**)&dcs, cs.size() * 4));
+      HIP_TRY(hipMemcpy(dcs, cs.data(), cs.size() * 4, hipMemcpyHostToDevice));
+      pa.rot = dcs;
+    }
+    VLA_TRY(al(&pa.u, (size_t)8 * nt * d * 2));
+    VLA_TRY(al(&pa.qkv, (size_t)8 * nt * (HT + 2) * hd * 2));
+    VLA_TRY(al(&pa.apart, (size_t)8 * pa.nsplit * nt * HT * hd * 2));
+    VLA_TRY(al((void**)&pa.astat, (size_t)8 * pa.nsplit * nt * HT * 2 * 4));
+    VLA_TRY(al(&pa.omerged, (size_t)8 * nt * HT * hd * 2));
+    VLA_TRY(al(&pa.hbuf, (size_t)8 * nt * (F / 8) * 2));
+    VLA_TRY(al((void**)&pa.delta, (size_t)2 * 8 * nt * d * 4));
     VLA_TRY(al((void**)&pa.sync, (size_t)PERSIST_SYNC_WORDS * 4));
     pa.err = reinterpret_cast<int*>(pa.sync + PERSIST_ERR_OFF);
     p->persist_err = pa.err;
@@ -624,7 +684,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
                             q.trace = *tracing ? tbuf : nullptr;
                             q.trace_all = *tracing == 2 ? 1 : 0;
                             q.spin_limit = *spin;
-                            e = launch_persist(q, s);
+                            e = persist_gate().launch(q, s);
                             if (e != hipSuccess) return e;
                             return hipMemcpyAsync(err_host, pa.err, 4, hipMemcpyDeviceToHost, s);
                           },
@@ -870,6 +930,7 @@ vla_status run_ops_profiled(Plan* p, hipStream_t s, int reps) {
 
 vla_model::~vla_model() {
   plans.clear();
+  if (persist_counted) persist_gate().add(-1);
   prefix_ws.clear();
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
   for (void* p : allocs) (void)hipFree(p);

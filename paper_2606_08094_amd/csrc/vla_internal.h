@@ -174,7 +174,7 @@ struct PLayer {
 };
 
 struct PersistArgs {
-  int L, d, H, G, hd, F, n, P, A, T;
+  int L, d, H, G, hd, F, n, P, A, T;   // n: token rows (the state token among them)
   int glu, act;              // MLP form: gate/up pair (1) or single W1 (0); activation
   int HT;                    // query heads per team (H / 8)
   int kba, nsplit;           // attention: 32-key blocks per split, key splits
@@ -188,7 +188,12 @@ struct PersistArgs {
   const void* e_pos;         // [n][d]
   const void* w_out;         // [A][d]
   const float* b_out;        // [A]
-  const float* a0;           // [n][A]: the noise chunk a_0
+  const float* a0;           // [n - stok][A]: the noise chunk a_0
+  // architecture variants (all off: the plain form of the kernel runs)
+  int causal;                // query t sees action keys 0 .. t only
+  int stok;                  // 1: token row 0 is the state token (xs alone), row t + 1 action t
+  const float* b_in;         // [d]: the action rows' input bias when stok (xs then holds the state row)
+  const float* rot;          // [n][hd / 2][2]: (cos, sin) of token row m's angles, NULL = no RoPE
   // team-replicated workspace (team = one of 8 groups of 32 workgroups)
   void* u;                   // [8][n][d]
   void* qkv;                 // [8][n][(HT + 2) hd]: team heads' Q, the team's K, V

@@ -79,8 +79,7 @@ def test_end_to_end(torch, name):
 def test_end_to_end_causal_variant(torch, name):
     """The causal action-token variant (VLA_OPT_CAUSAL_SELF) end to end against
     the oracle with the same mask, under the default loop driver (for pi0 the
-    persistent kernel is unmasked, so the graph driver runs); the mask changes
-    the chunk."""
+    persistent kernel); the mask changes the chunk."""
     from vla_testlib import workload
     cfg0, W, inp = workload(name, 1)
     cfg = cfg0.with_(n_steps=3, causal_self=True)

@@ -88,6 +88,82 @@ def test_persist_matches_oracle_and_graph(torch, case):
     assert np.array_equal(got[0], got[1]), "persistent driver is not deterministic"
 
 
+VARIANTS = {
+    # each option alone and all together, at the kernel's edges: one row tile to
+    # four (the state token adds a row), a second block of chunk keys that a
+    # causal query does not see, head widths and two heads per team
+    "causal_20": SMALL.with_(name="v_c20", n_action=20, prefix_len=37, n_steps=2, causal_self=True, seed_base=6700),
+    "causal_32_h16": SMALL.with_(name="v_c32", n_heads=16, n_kv_heads=2, n_action=32, prefix_len=70, n_steps=2,
+                                 causal_self=True, mlp="swiglu", seed_base=6710),
+    "rope_50": SMALL.with_(name="v_r50", n_action=50, prefix_len=100, n_steps=2, rope_base=10000.0, seed_base=6720),
+    "rope_h16_hd64": SMALL.with_(name="v_r16", n_heads=16, n_kv_heads=2, n_action=17, prefix_len=33, n_steps=2,
+                                 rope_base=100.0, seed_base=6730),
+    "state_1_plus_1": SMALL.with_(name="v_s1", n_action=1, prefix_len=5, n_steps=2, state_token=True, seed_base=6740),
+    "state_50": SMALL.with_(name="v_s50", n_action=50, prefix_len=64, n_steps=3, state_token=True, seed_base=6750),
+    "all_49": SMALL.with_(name="v_a49", n_action=49, prefix_len=65, n_steps=2, causal_self=True, rope_base=10000.0,
+                          state_token=True, seed_base=6760),
+    "all_51_d1024_hd256": SMALL.with_(name="v_a51", d_model=1024, head_dim=256, d_ff=4096, d_prefix=1024, n_action=51,
+                                      prefix_len=90, n_steps=2, causal_self=True, rope_base=10000.0, state_token=True,
+                                      seed_base=6770),
+    "all_52_hd128": SMALL.with_(name="v_a52", head_dim=128, n_action=52, prefix_len=31, n_steps=1, causal_self=True,
+                                rope_base=500.0, state_token=True, seed_base=6780),
+    "all_20_hd256": SMALL.with_(name="v_a20", head_dim=256, n_action=20, prefix_len=40, n_steps=2, causal_self=True,
+                                rope_base=10000.0, state_token=True, seed_base=6800),
+    "all_30_d1024_hd64": SMALL.with_(name="v_a30", d_model=1024, d_ff=4096, d_prefix=1024, n_action=30, prefix_len=77,
+                                     n_steps=2, causal_self=True, rope_base=10000.0, state_token=True, seed_base=6810),
+    "all_63_d1024": SMALL.with_(name="v_a63", d_model=1024, head_dim=128, d_ff=4096, d_prefix=1024, n_action=63,
+                                prefix_len=97, n_steps=2, causal_self=True, rope_base=10000.0, state_token=True,
+                                seed_base=6790),
+}
+
+
+@pytest.mark.parametrize("case", sorted(VARIANTS))
+def test_persist_variants_match_oracle_and_graph(torch, case):
+    """Causal action tokens, RoPE and the state token in the persistent kernel."""
+    cfg = VARIANTS[case]
+    W = wl.make_weights(cfg)
+    inp = wl.make_batch(cfg, 1)
+    tau = wl.uniform_schedule(cfg.n_steps)
+    cache = O.prefix_kv_build(cfg, W, inp["prefix"])
+    ref = O.denoise(cfg, W, cache, inp["noise"], inp["state"], tau)
+    got = _run(cfg, W, inp, tau, loop_mode=2, reps=2)
+    graph = _run(cfg, W, inp, tau, loop_mode=1)[0]
+    err, dg = np.abs(got[0] - ref).max(), np.abs(got[0] - graph).max()
+    print(f"{case}: persistent vs oracle max|d| = {err:.3e}, vs graph driver {dg:.3e}")
+    assert np.all(np.isfinite(got[0]))
+    assert err <= TOL, f"{case}: max|d| {err}"
+    assert dg <= TOL
+    assert np.array_equal(got[0], got[1]), "persistent driver is not deterministic"
+
+
+def test_persist_two_models_on_two_streams(torch):
+    """Persistent calls of two models on two streams at once: neither starves
+    the other of compute units (no barrier times out), both match their own
+    result alone."""
+    from vla_testlib import Pipeline
+    cfgs = [CASES["small_geglu"], VARIANTS["all_49"]]
+    tau = [wl.uniform_schedule(c.n_steps) for c in cfgs]
+    pipes = [Pipeline(c, wl.make_weights(c), wl.make_batch(c, 1), 2) for c in cfgs]
+    try:
+        alone = []
+        for p, t in zip(pipes, tau):
+            p.build_cache()
+            alone.append(p.denoise(t).cpu().numpy().copy())
+        streams = [torch.cuda.Stream() for _ in pipes]
+        torch.cuda.synchronize()
+        for _ in range(20):
+            for p, t, s in zip(pipes, tau, streams):
+                with torch.cuda.stream(s):
+                    p.denoise(t)
+        torch.cuda.synchronize()
+        for p, a in zip(pipes, alone):
+            p.model.check()
+            assert np.array_equal(p.out.cpu().numpy(), a)
+    finally:
+        for p in pipes:
+            p.close()
+
+
 def test_persist_pi0_full(torch):
     """The full pi0-shaped workload (18 layers, 816 prefix rows, T = 10) with
     denormalisation statistics."""
