@@ -10,6 +10,8 @@
 // range (its K-slices one after another); only the raw int32 entry splits K
 // across workgroups, adding the exact partial sums atomically.  The
 // dequantised path with few token rows uses tern_skinny instead.
+#include <algorithm>
+
 #include "gemm_epilogue.h"
 
 namespace {
@@ -37,8 +39,37 @@ VLA_DEV int sum_i8x16(uint4 v) {
   return s;
 }
 
-// Requires K % 64 == 0 (16-byte aligned packed rows).
-template <int MS, int NSUB, int NC>
+// The model layout: a weight in two's complement (00, 01, 11 for 0, +1, -1),
+// four to a byte, with weights 4 i + j of a dword's 16 (i, j < 4) in bits
+// 2i..2i+1 of byte j.  Widening is a shift and a mask per output dword: bits
+// 7..6 of each byte are the weight and the rest zero, so the four bytes are
+// 64 w of four consecutive k, and the exact sum of 64 q w shifts right by 6
+// (|q w| sums stay below 2^23 for K <= 2^16, so 64 of them fit in 32 bits).
+// Seven instructions a dword, against 19 for the codes of the ABI's layout
+// (its masks and byte permutes) and 23 for signed weights from them.
+VLA_DEV i32x4 widen64(uint32_t p) {
+  return i32x4{(int)((p << 6) & 0xC0C0C0C0u), (int)((p << 4) & 0xC0C0C0C0u), (int)((p << 2) & 0xC0C0C0C0u),
+               (int)(p & 0xC0C0C0C0u)};
+}
+
+// ABI layout -> model layout, in place, one dword (16 weights) per thread and
+// step.  A code of 3 is undefined input.
+__global__ __launch_bounds__(256) void tern_repack_kernel(uint32_t* w, size_t n) {
+  for (size_t t = blockIdx.x * (size_t)256 + threadIdx.x; t < n; t += (size_t)gridDim.x * 256) {
+    const uint32_t p = w[t];
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {   // weight k: byte k / 4, field k % 4 -> byte k % 4, field k / 4
+      const uint32_t c = (p >> (8 * (k >> 2) + 2 * (k & 3))) & 3u;
+      r |= ((c + 3u) & 3u) << (8 * (k & 3) + 2 * (k >> 2));   // w = c - 1 mod 4
+    }
+    w[t] = r;
+  }
+}
+
+// Requires K % 64 == 0 (16-byte aligned packed rows).  RP: weights in the
+// model layout (64 w, no row sums needed), else codes of the ABI's.
+template <int MS, int NSUB, int NC, bool RP>
 __global__ __launch_bounds__(256) void tern_kernel(TernArgs a) {
   constexpr int KC = 256;  // 4 lane groups x 64 k
   constexpr int KS = NC * KC;
@@ -94,7 +125,7 @@ __global__ __launch_bounds__(256) void tern_kernel(TernArgs a) {
       uint4 v = make_uint4(0, 0, 0, 0);
       if (m < M && k < send) {
         v = ldg16(a.x + (size_t)m * K + k);
-        atomicAdd(&rsum_s[row], sum_i8x16(v));
+        if (!RP) atomicAdd(&rsum_s[row], sum_i8x16(v));
       }
       *reinterpret_cast<uint4*>(xs + (size_t)row * PITCH + kv * 16) = v;
     }
@@ -114,7 +145,8 @@ __global__ __launch_bounds__(256) void tern_kernel(TernArgs a) {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             acc[ms][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, xf[r]),
-                                                               unpack_codes(pw[r]), acc[ms][s], 0, 0, 0);
+                                                               RP ? widen64(pw[r]) : unpack_codes(pw[r]), acc[ms][s],
+                                                               0, 0, 0);
         }
       }
     }
@@ -125,9 +157,9 @@ __global__ __launch_bounds__(256) void tern_kernel(TernArgs a) {
   for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int rs = rsum_s[ms * 16 + g4 * 4 + i];
+      const int rs = RP ? 0 : rsum_s[ms * 16 + g4 * 4 + i];
 #pragma unroll
-      for (int s = 0; s < NSUB; ++s) acc[ms][s][i] -= rs;
+      for (int s = 0; s < NSUB; ++s) acc[ms][s][i] = RP ? acc[ms][s][i] >> 6 : acc[ms][s][i] - rs;
     }
 
   if (a.nsplit > 1 && a.rscale == nullptr) {
@@ -213,9 +245,9 @@ VLA_DEV i32x4 unpack_signed(uint32_t p) {
 // gate/up pair of 16-row blocks for GLU) and every token row (M <= 16 MS).
 // K is cut into chunks of 256 (4 lane groups x 64); wave w takes chunks w,
 // w+4, ..., and issues all W and X loads of up to CPW chunks before their
-// MFMAs.  Weights are widened to signed int8, so the MFMA sums q * w
-// directly; the four waves' int32 partials are added through LDS (exact),
-// then waves 0 .. MS-1 dequantise and run the epilogue of one 16-row subtile.
+// MFMAs.  Weights come in the model layout, so the MFMA sums 64 q w; the four
+// waves' int32 partials are added through LDS and shifted back (exact), then
+// waves 0 .. MS-1 dequantise and run the epilogue of one 16-row subtile.
 template <int MS, int NSUB, int CPW>
 __global__ __launch_bounds__(256) void tern_skinny(TernArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -259,7 +291,7 @@ __global__ __launch_bounds__(256) void tern_skinny(TernArgs a) {
         const uint32_t pw[4] = {wreg[j][s].x, wreg[j][s].y, wreg[j][s].z, wreg[j][s].w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const i32x4 wv = unpack_signed(pw[r]);
+          const i32x4 wv = widen64(pw[r]);
 #pragma unroll
           for (int ms = 0; ms < MS; ++ms)
             acc[ms][s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, xreg[j][ms][r]), wv, acc[ms][s], 0, 0, 0);
@@ -289,7 +321,7 @@ __global__ __launch_bounds__(256) void tern_skinny(TernArgs a) {
     for (int i = 0; i < 4; ++i) {
       const int m = ms * 16 + g4 * 4 + i;
       const float rm = (m < M) ? a.rscale[m] : 0.0f;
-      y[0][s][i] = (float)t[i] * (sw[s] * rm / 127.0f);
+      y[0][s][i] = (float)(t[i] >> 6) * (sw[s] * rm / 127.0f);
     }
   }
   wave_epilogue<bf16_t, 1, NSUB>(a.e, y, ms * 16, n0, 0);
@@ -401,7 +433,8 @@ template <int MS, int NSUB, int NC>
 hipError_t tern_launch(const TernArgs& a, int units, hipStream_t s) {
   constexpr int MT = 16 * MS;
   const size_t lds = (size_t)MT * (NC * 256 + 16) + (size_t)MT * 4;
-  hipLaunchKernelGGL((tern_kernel<MS, NSUB, NC>), dim3(units), dim3(256), lds, s, a);
+  if (a.model_layout) hipLaunchKernelGGL((tern_kernel<MS, NSUB, NC, true>), dim3(units), dim3(256), lds, s, a);
+  else hipLaunchKernelGGL((tern_kernel<MS, NSUB, NC, false>), dim3(units), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 
@@ -420,7 +453,7 @@ hipError_t tern_nc(int nc, const TernArgs& a, int units, hipStream_t s) {
 
 hipError_t launch_ternary_dot4(const TernArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  if (a.K % 64 != 0 || a.rscale == nullptr || a.e.epi != EPI_STORE) return hipErrorInvalidValue;
+  if (a.K % 64 != 0 || a.rscale == nullptr || a.e.epi != EPI_STORE || a.model_layout) return hipErrorInvalidValue;
   static bool attr = false;
   if (!attr) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tern_dot4),
@@ -453,6 +486,16 @@ namespace {
 // NWV waves of 32 columns each: a 128-column tile on four waves, or a
 // 256-column one on eight, whose K-slice (codes + weights) then feeds twice
 // the MFMAs for 1.2x (MS = 4) the bytes.
+template <int RS, int NS>
+VLA_DEV void shift_back(i32x4 (&acc)[RS][NS]) {   // sums of 64 q w -> sums of q w
+#pragma unroll
+  for (int ms = 0; ms < RS; ++ms)
+#pragma unroll
+    for (int ns = 0; ns < NS; ++ns)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[ms][ns][i] >>= 6;
+}
+
 template <int MS, int NWV = 4>
 struct TRing {
   static constexpr int BM = 32 * MS, BN = 32 * NWV;
@@ -467,7 +510,8 @@ struct TRing {
   static_assert(LX >= 1 && LX * 64 * NWV == SX, "code rows per wave");
 };
 
-template <int MS, int NWV = 4>
+// RP: weights in the model layout, else the ABI's codes.
+template <int MS, int NWV, bool RP>
 __global__ __launch_bounds__(64 * NWV) void tern_tile(TernArgs a) {
   using R = TRing<MS, NWV>;
   constexpr int BM = R::BM, BN = R::BN, SX = R::SX, SB = R::SB, NST = R::NST, LX = R::LX, D = NST - 1;
@@ -533,7 +577,7 @@ __global__ __launch_bounds__(64 * NWV) void tern_tile(TernArgs a) {
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int ns = 0; ns < 2; ++ns) {
-        const i32x4 w = unpack_signed(wp[kk][ns]);
+        const i32x4 w = RP ? widen64(wp[kk][ns]) : unpack_signed(wp[kk][ns]);
 #pragma unroll
         for (int ms = 0; ms < RS; ++ms)
           acc[ms][ns] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, xf[kk][ms]), w, acc[ms][ns],
@@ -563,6 +607,7 @@ __global__ __launch_bounds__(64 * NWV) void tern_tile(TernArgs a) {
     }(std::make_integer_sequence<int, NST>{});
   }
 
+  if (RP) shift_back(acc);
   const int nw = n0 + wave * 32;
   if (a.rscale == nullptr) {   // raw int32 sums
 #pragma unroll
@@ -615,7 +660,7 @@ __global__ __launch_bounds__(64 * NWV) void tern_tile(TernArgs a) {
 // stream into a ring of NPR pairs (each stage laid out as tern_tile's),
 // NPR - 1 pairs ahead of the MFMAs.  At the end group 1 hands its int32
 // sums to group 0 through LDS (exact), and group 0 runs the epilogue.
-template <int MS>
+template <int MS, bool RP>
 __global__ __launch_bounds__(512) void tern_tile_kg(TernArgs a) {
   using R = TRing<MS, 4>;
   constexpr int BM = R::BM, BN = R::BN, SX = R::SX, SB = R::SB, LX = R::LX;
@@ -683,7 +728,7 @@ __global__ __launch_bounds__(512) void tern_tile_kg(TernArgs a) {
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
       for (int ns = 0; ns < 2; ++ns) {
-        const i32x4 w = unpack_signed(wp[kk][ns]);
+        const i32x4 w = RP ? widen64(wp[kk][ns]) : unpack_signed(wp[kk][ns]);
 #pragma unroll
         for (int ms = 0; ms < RS; ++ms)
           acc[ms][ns] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(i32x4, xf[kk][ms]), w, acc[ms][ns],
@@ -722,6 +767,7 @@ __global__ __launch_bounds__(512) void tern_tile_kg(TernArgs a) {
 #pragma unroll
     for (int ns = 0; ns < 2; ++ns) acc[ms][ns] += red[((wl * RS + ms) * 2 + ns) * 64 + lane];
 
+  if (RP) shift_back(acc);
   const int nw = n0 + wl * 32;
   if (a.rscale == nullptr) {   // raw int32 sums
 #pragma unroll
@@ -773,7 +819,8 @@ hipError_t tile_kg_launch(const TernArgs& a0, hipStream_t s) {
   a.n_tiles = (a.N + 127) / 128;
   const int tiles = a.m_tiles * a.n_tiles;
   const int grid = (tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((tern_tile_kg<MS>), dim3(grid), dim3(512), 0, s, a);
+  if (a.model_layout) hipLaunchKernelGGL((tern_tile_kg<MS, true>), dim3(grid), dim3(512), 0, s, a);
+  else hipLaunchKernelGGL((tern_tile_kg<MS, false>), dim3(grid), dim3(512), 0, s, a);
   return hipGetLastError();
 }
 
@@ -784,11 +831,21 @@ hipError_t tile_launch(const TernArgs& a0, hipStream_t s) {
   a.n_tiles = (a.N + 32 * NWV - 1) / (32 * NWV);
   const int tiles = a.m_tiles * a.n_tiles;
   const int grid = (tiles + 7) / 8 * 8;
-  hipLaunchKernelGGL((tern_tile<MS, NWV>), dim3(grid), dim3(64 * NWV), 0, s, a);
+  if (a.model_layout) hipLaunchKernelGGL((tern_tile<MS, NWV, true>), dim3(grid), dim3(64 * NWV), 0, s, a);
+  else hipLaunchKernelGGL((tern_tile<MS, NWV, false>), dim3(grid), dim3(64 * NWV), 0, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
+
+hipError_t launch_ternary_repack(void* w, size_t bytes, hipStream_t s) {
+  if (bytes % 4) return hipErrorInvalidValue;
+  const size_t n = bytes / 4;
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(tern_repack_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s,
+                     reinterpret_cast<uint32_t*>(w), n);
+  return hipGetLastError();
+}
 
 bool tern_tile_eligible(int M, int N, int K) { return M >= 128 && N >= 1 && K >= 128 && K % 128 == 0; }
 
@@ -811,7 +868,7 @@ hipError_t launch_ternary_tile(const TernArgs& a, int ms, int waves, int kgroups
 hipError_t launch_ternary_gemm(const TernArgs& a, int ms, int units, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.K % 64 != 0) {
-    if (a.rscale != nullptr) return hipErrorInvalidValue;
+    if (a.rscale != nullptr || a.model_layout) return hipErrorInvalidValue;
     const long long total = (long long)a.M * a.N;
     hipLaunchKernelGGL(tern_generic_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a.x, a.w, a.M,
                        a.N, a.K, a.acc_out);
@@ -829,7 +886,7 @@ hipError_t launch_ternary_gemm(const TernArgs& a, int ms, int units, hipStream_t
     if (t28 >= 256) return tile_launch<2, 8>(a, s);
     return t4 >= 256 ? tile_launch<4>(a, s) : t2 >= 128 ? tile_kg_launch<2>(a, s) : tile_kg_launch<1>(a, s);
   }
-  if (a.rscale != nullptr && a.M <= 64) {  // token rows of the denoise loop: the skinny kernel
+  if (a.rscale != nullptr && a.M <= 64 && a.model_layout) {  // token rows of the denoise loop: the skinny kernel
     const int sms = a.M <= 16 ? 1 : (a.M <= 32 ? 2 : 4);
     switch (sms * 10 + nsub) {
       case 11: return skinny_launch<1, 1>(a, s);

@@ -329,6 +329,7 @@ struct Builder {
     a.ks = t.nc * 256;
     a.nsplit = 1;
     a.n_tiles = t.n_tiles;
+    a.model_layout = 1;
     double ob = a.e.out_f32 ? 4.0 : 2.0;
     if (a.e.epi == EPI_RESID) ob = 8.0;
     if (a.e.epi == EPI_GLU) ob = 2.0;
@@ -416,7 +417,6 @@ int mlp_act(int mlp) {
   }
 }
 
-// The persistent step kernel covers the batch-1 bf16 dense expert with joint
 // The persistent kernel needs every compute unit at once, so two of them must
 // not be dispatched side by side (two models on two streams): each would hold
 // part of the device and wait for the rest.  As soon as a second live model
@@ -457,6 +457,7 @@ PersistGate& persist_gate() {
   return *g;
 }
 
+// The persistent step kernel covers the batch-1 bf16 dense expert with joint
 // attention whose shape fits its team layout (see persist_supported).
 bool persist_eligible(vla_model* m, int B, int P, int T) {
   const vla_config& c = m->cfg;
@@ -562,11 +563,11 @@ vla_status build_plan(vla_model* m, Plan* p) {
   }
 
   if (p->persist) {
-    PersistArgs pa{};
     if (!m->persist_counted) {
       persist_gate().add(1);
       m->persist_counted = true;
     }
+    PersistArgs pa{};
     pa.L = L; pa.d = d; pa.H = c.n_heads; pa.G = c.n_kv_heads; pa.hd = hd; pa.F = F; pa.n = nt; pa.P = P;
     pa.A = A; pa.T = T;
     pa.glu = c.mlp != VLA_MLP_GELU;
@@ -625,7 +626,6 @@ vla_status build_plan(vla_model* m, Plan* p) {
     pa.w_out = m->W_out;
     pa.b_out = m->b_out;
     pa.a0 = p->a;
-    const int HT = pa.HT;
     pa.causal = m->causal;
     pa.stok = m->state_token;
     pa.b_in = m->b_in;
@@ -643,6 +643,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
       HIP_TRY(hipMemcpy(dcs, cs.data(), cs.size() * 4, hipMemcpyHostToDevice));
       pa.rot = dcs;
     }
+    const int HT = pa.HT;
     VLA_TRY(al(&pa.u, (size_t)8 * nt * d * 2));
     VLA_TRY(al(&pa.qkv, (size_t)8 * nt * (HT + 2) * hd * 2));
     VLA_TRY(al(&pa.apart, (size_t)8 * pa.nsplit * nt * HT * hd * 2));
@@ -673,7 +674,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
       (void)ml;
     }
     const double cbytes = (double)L * 2 * c.n_kv_heads * P * hd * es;
-    const double gflop = (double)T * (2.0 * n * wbytes / es + 4.0 * n * c.n_heads * hd * (P + n) * L);
+    const double gflop = (double)T * (2.0 * nt * wbytes / es + 4.0 * nt * c.n_heads * hd * (P + nt) * L);
     // Every launch starts from cleared barrier flags, rank counters and error
     // word; the error word is copied to pinned host memory after the kernel,
     // where the next call (or vla_model_check) finds it.
@@ -688,7 +689,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
                             if (e != hipSuccess) return e;
                             return hipMemcpyAsync(err_host, pa.err, 4, hipMemcpyDeviceToHost, s);
                           },
-                          op_info(VLA_OP_PERSIST, n, L, T, (double)T * (wbytes + cbytes), gflop)});
+                          op_info(VLA_OP_PERSIST, nt, L, T, (double)T * (wbytes + cbytes), gflop)});
     HIP_TRY(hipDeviceSynchronize());
     return VLA_OK;
   }
@@ -929,8 +930,8 @@ vla_status run_ops_profiled(Plan* p, hipStream_t s, int reps) {
 }  // namespace
 
 vla_model::~vla_model() {
-  plans.clear();
   if (persist_counted) persist_gate().add(-1);
+  plans.clear();
   prefix_ws.clear();
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
   for (void* p : allocs) (void)hipFree(p);
@@ -1125,6 +1126,7 @@ vla_status fuse(vla_model* m, void** dst, float** scales, const std::vector<Part
       for (int i = 0; i < p.rows; ++i) sc.push_back(p.scale);
     }
   }
+  if (tern) HIP_TRY(launch_ternary_repack(*dst, (size_t)rows * rowbytes, nullptr));
   if (tern && scales) VLA_TRY(upload_scales(m, scales, sc));
   return VLA_OK;
 }
@@ -1403,7 +1405,7 @@ static vla_status prefix_kv_build_impl(vla_model* m, const void* prefix_hidden, 
         TernArgs ta{};
         const Tiling t = tern_tiling(M, N, K, 1);
         ta.M = M; ta.N = N; ta.K = K; ta.x = q8; ta.w = (const uint8_t*)sw.kvc; ta.rscale = r8;
-        ta.wscale = sw.s_kvc; ta.ks = t.nc * 256; ta.nsplit = 1; ta.n_tiles = t.n_tiles; ta.e = g;
+        ta.wscale = sw.s_kvc; ta.ks = t.nc * 256; ta.nsplit = 1; ta.n_tiles = t.n_tiles; ta.e = g; ta.model_layout = 1;
         HIP_TRY(launch_ternary_gemm(ta, t.ms, t.units, s));
       }
     }
@@ -1784,7 +1786,11 @@ vla_status vla_test_ternary_linear(const float* x, const uint8_t* w_packed, int3
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const Tiling t = tern_tiling(M, N, K, 1);
   int8_t* q8 = nullptr;
+  uint8_t* w = nullptr;   // the weights in the model layout
   float *r8 = nullptr, *sc = nullptr;
+  HIP_TRY(hipMalloc(&w, (size_t)N * K / 4));
+  HIP_TRY(hipMemcpyAsync(w, w_packed, (size_t)N * K / 4, hipMemcpyDeviceToDevice, s));
+  HIP_TRY(launch_ternary_repack(w, (size_t)N * K / 4, s));
   HIP_TRY(hipMalloc(&q8, (size_t)M * K));
   HIP_TRY(hipMalloc(&r8, (size_t)M * 4));
   HIP_TRY(hipMalloc(&sc, (size_t)N * 4));
@@ -1793,13 +1799,13 @@ vla_status vla_test_ternary_linear(const float* x, const uint8_t* w_packed, int3
   QuantArgs qa{};
   qa.M = M; qa.K = K; qa.x = x; qa.ldx = K; qa.src_type = 0; qa.q = q8; qa.r = r8;
   TernArgs a{};
-  a.M = M; a.N = N; a.K = K; a.x = q8; a.w = w_packed; a.rscale = r8; a.wscale = sc;
-  a.ks = t.nc * 256; a.nsplit = 1; a.n_tiles = t.n_tiles;
+  a.M = M; a.N = N; a.K = K; a.x = q8; a.w = w; a.rscale = r8; a.wscale = sc;
+  a.ks = t.nc * 256; a.nsplit = 1; a.n_tiles = t.n_tiles; a.model_layout = 1;
   a.e.M = M; a.e.N = N; a.e.K = K; a.e.epi = EPI_STORE; a.e.out = y; a.e.ldo = N; a.e.out_f32 = 1;
   hipError_t e = launch_quantize(qa, s);
   if (e == hipSuccess) e = launch_ternary_gemm(a, t.ms, t.units, s);
   hipError_t e2 = hipStreamSynchronize(s);
-  (void)hipFree(q8); (void)hipFree(r8); (void)hipFree(sc);
+  (void)hipFree(q8); (void)hipFree(r8); (void)hipFree(sc); (void)hipFree(w);
   if (e != hipSuccess || e2 != hipSuccess)
     return fail(VLA_E_DEVICE, "ternary linear: %s", hipGetErrorString(e != hipSuccess ? e : e2));
   return VLA_OK;
@@ -1821,6 +1827,14 @@ vla_status vla_test_ternary_gemm(const int8_t* q, const float* r, const uint8_t*
   a.M = M; a.N = N; a.K = K; a.x = q; a.w = w_packed; a.rscale = r; a.wscale = wscale;
   a.ks = t.nc * 256; a.nsplit = 1; a.n_tiles = t.n_tiles;
   a.e.M = M; a.e.N = N; a.e.K = K; a.e.epi = EPI_STORE; a.e.out = y; a.e.ldo = N; a.e.out_f32 = 1;
+  uint8_t* w = nullptr;
+  if (variant != 1) {   // the dot4 kernel reads the ABI's layout, the model's kernels their own
+    HIP_TRY(hipMalloc(&w, (size_t)N * K / 4));
+    HIP_TRY(hipMemcpyAsync(w, w_packed, (size_t)N * K / 4, hipMemcpyDeviceToDevice, s));
+    HIP_TRY(launch_ternary_repack(w, (size_t)N * K / 4, s));
+    a.w = w;
+    a.model_layout = 1;
+  }
   auto run = [&]() {
     // (row tile / 32, waves, K groups)
     static const int tile_cfg[8][3] = {{1, 4, 1}, {2, 4, 1}, {4, 4, 1}, {2, 8, 1}, {4, 8, 1}, {1, 8, 2}, {2, 8, 2},
@@ -1841,6 +1855,7 @@ vla_status vla_test_ternary_gemm(const int8_t* q, const float* r, const uint8_t*
   if (e == hipSuccess && e2 == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
+  if (w) (void)hipFree(w);
   if (e != hipSuccess || e2 != hipSuccess)
     return fail(VLA_E_DEVICE, "ternary gemm: %s", hipGetErrorString(e != hipSuccess ? e : e2));
   if (us_per_launch) *us_per_launch = 1000.0f * ms / (float)iters;

@@ -138,6 +138,7 @@ struct TernArgs {
   int M, N, K;
   const int8_t* x;         // [M][K]
   const uint8_t* w;        // [N][K/4] packed
+  int model_layout;        // 1: w in the model layout (launch_ternary_repack), 0: the ABI's codes
   const float* rscale;     // [M] absmax per row (dequant) or NULL for raw acc
   const float* wscale;     // [N] per W-row scale (the per-tensor scale of its matrix)
   int32_t* acc_out;        // raw int32 output (when rscale == NULL); zero-filled if nsplit > 1
@@ -261,6 +262,9 @@ hipError_t launch_time_embed(int et, const CallParams* cp, void* e, int T, int T
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s);
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t s);
 hipError_t launch_ternary_dot4(const TernArgs& a, hipStream_t s);   // VALU sdot4 variant (EPI_STORE)
+// Packed ternary weights from the ABI's layout to the one the model's kernels
+// widen (in place; whole rows of K % 16 == 0).
+hipError_t launch_ternary_repack(void* w, size_t bytes, hipStream_t s);
 // The tiled W2A8 kernel takes the shape (many token rows, K % 128 == 0).
 bool tern_tile_eligible(int M, int N, int K);
 // The tiled W2A8 kernel with (32 ms)-row tiles (ms 1, 2 or 4) on `waves`
