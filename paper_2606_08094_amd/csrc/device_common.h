@@ -87,6 +87,24 @@ VLA_DEV uint4 ldg16(const void* p) {
   const gv4u_t v = *(const global_v4u*)(p);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+// Tiled operands: k-steps of KS = 64 bytes of a row (one 16-byte vector per
+// lane group of an MFMA operand).  Activations are [K / KS][rows][KS] with the
+// row count padded to 16, weights [N / 16][K / KS][16][KS], so the 16 rows of
+// an operand's k-step are one contiguous kilobyte: a wave-wide load of it
+// touches 8 whole cache lines where rows of a row-major matrix give 16 halves.
+template <typename T> VLA_DEV size_t xtile_off(int row, int k, int rows_pad) {
+  constexpr int KS = 4 * ElemTraits<T>::E;
+  return ((size_t)(k / KS) * rows_pad + row) * KS + k % KS;
+}
+template <typename T> VLA_DEV size_t wtile_off(int n, int k, int ktiles) {
+  constexpr int KS = 4 * ElemTraits<T>::E;
+  return ((size_t)(n >> 4) * ktiles + k / KS) * (16 * KS) + (n & 15) * KS + k % KS;
+}
+// Element (row, k) of an activation written tiled (rows_pad > 0) or row-major.
+template <typename T> VLA_DEV size_t act_off(int row, int k, int ld, int rows_pad) {
+  return rows_pad ? xtile_off<T>(row, k, rows_pad) : (size_t)row * ld + k;
+}
+
 // Buffer loads: a resource over [base, base + bytes); loads past its end (kOob
 // always is, for buffers below 2 GiB) read zero without a branch.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -94,8 +112,8 @@ constexpr unsigned kOob = 0x7ffffff0u;
 VLA_DEV rsrc_t make_rsrc(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
-VLA_DEV uint4 buf_ld16(rsrc_t r, unsigned off) {
-  const gv4u_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+VLA_DEV uint4 buf_ld16(rsrc_t r, unsigned off, unsigned soff = 0) {   // soff: wave-uniform
+  const gv4u_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 VLA_DEV void stg16(void* p, uint4 v) { *reinterpret_cast<uint4*>(p) = v; }

@@ -29,7 +29,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs& a, const f32x4 (&a
               if (a.out_f32)
                 reinterpret_cast<float*>(a.out)[(size_t)m * a.ldo + n] = v;
               else
-                reinterpret_cast<T*>(a.out)[(size_t)m * a.ldo + n] = ElemTraits<T>::from_f(v);
+                reinterpret_cast<T*>(a.out)[act_off<T>(m, n, a.ldo, a.ot)] = ElemTraits<T>::from_f(v);
             }
           }
         }
@@ -75,7 +75,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmArgs& a, const f32x4 (&a
               if (a.out_f32)
                 reinterpret_cast<float*>(a.out)[(size_t)m * a.ldo + f] = h;
               else
-                reinterpret_cast<T*>(a.out)[(size_t)m * a.ldo + f] = ElemTraits<T>::from_f(h);
+                reinterpret_cast<T*>(a.out)[act_off<T>(m, f, a.ldo, a.ot)] = ElemTraits<T>::from_f(h);
             }
           }
       }

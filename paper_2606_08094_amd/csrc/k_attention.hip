@@ -315,9 +315,9 @@ __global__ __launch_bounds__(512) void attn_kernel(AttnArgs a) {
     }
   };
   if (a.kv_split == 1) {
-    T* op = reinterpret_cast<T*>(a.o) + (size_t)(b * a.n + qrow) * a.ldo + h * HD;
+    T* op = reinterpret_cast<T*>(a.o);
 #pragma unroll
-    for (int d = 0; d < DT; ++d) put4(op + d * 16 + 4 * g4, o[d]);
+    for (int d = 0; d < DT; ++d) put4(op + act_off<T>(b * a.n + qrow, h * HD + d * 16 + 4 * g4, a.ldo, a.o_rows), o[d]);
     return;
   }
   // partial: normalised by its own sum, plus (max, sum)
@@ -392,7 +392,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(AttnArgs a) {
   const float inv = tot > 0.0f ? 1.0f / tot : 0.0f;
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] *= inv;
-  stg16(reinterpret_cast<T*>(a.o) + (size_t)m * a.ldo + c, pack16(acc, T()));
+  stg16(reinterpret_cast<T*>(a.o) + act_off<T>(m, c, a.ldo, a.o_rows), pack16(acc, T()));
 }
 
 template <typename T>
@@ -747,10 +747,9 @@ __global__ __launch_bounds__(64 * TW) void attn_tile(AttnArgs a) {
   const int rows = a.B * a.n, dq = a.H * HD;
   const int hh = R / a.n, t = R - hh * a.n, h = g * per + hh;
   const float inv = lrun > 0.f ? 1.f / lrun : 0.f;
-  bf16_t* dst;
-  if (a.kv_split == 1) {
-    dst = reinterpret_cast<bf16_t*>(a.o) + (size_t)(b * a.n + t) * a.ldo + h * HD;
-  } else {
+  const bool whole = a.kv_split == 1;
+  bf16_t* dst = reinterpret_cast<bf16_t*>(a.o);
+  if (!whole) {
     dst = reinterpret_cast<bf16_t*>(a.part) + ((size_t)split * rows + b * a.n + t) * dq + h * HD;
     if (g4 == 0) {
       float* st = a.stats + (((size_t)split * rows + b * a.n + t) * a.H + h) * 2;
@@ -760,7 +759,8 @@ __global__ __launch_bounds__(64 * TW) void attn_tile(AttnArgs a) {
   }
 #pragma unroll
   for (int d = 0; d < DT; ++d)
-    *reinterpret_cast<uint2*>(dst + d * 16 + 4 * g4) =
+    *reinterpret_cast<uint2*>(dst + (whole ? act_off<bf16_t>(b * a.n + t, h * HD + d * 16 + 4 * g4, a.ldo, a.o_rows)
+                                           : (size_t)(d * 16 + 4 * g4))) =
         make_uint2(pack_bf16x2(o[d][0] * inv, o[d][1] * inv), pack_bf16x2(o[d][2] * inv, o[d][3] * inv));
 }
 

@@ -18,8 +18,9 @@
 //   the fixed latency of a launch, so the tile is the one that spreads the
 //   least bytes over 256 compute units (skinny_cost).  In a chain of cold
 //   weights, against tiles that always hold every token row with branchy loads
-//   in 128-wide chunks (50 rows, bf16): 960 x 720 5.7 -> 3.7 us, 1600 x 720
-//   5.8 -> 4.2, gate/up 4096 x 720 6.2 -> 5.2.
+//   in 128-wide chunks (50 rows, bf16): 960 x 720 5.7 -> 3.6 us, 1600 x 720
+//   5.8 -> 3.9, gate/up 4096 x 720 6.2 -> 4.8 (row-major operands: 3.8, 4.2, 5.2),
+//   down 720 x 2048 4.7 -> 3.5; 51 rows, 8192 x 1024 9.4 -> 7.2.
 //
 // gemm_wide -- fp32 with M > 128.  Four waves along N (NT = 64*NSUB), X
 //   staged per K-slice in LDS and shared by the four waves, K-slices looped
@@ -82,8 +83,10 @@ VLA_DEV void stage_x(const GemmArgs& a, T* xs, int pitch, int m0, int k0, int KW
 }
 
 // ---------------------------------------------------------------------------
-// NV: 4 E-wide k-steps of one wave and round (E values per 16-byte vector).
-template <typename T, int MS, int NSUB, int NV>
+// NV: k-steps (4 E values: one 16-byte vector per lane group) of one wave and
+// round.  TL: both operands tiled (device_common.h): every load is one whole
+// kilobyte at a wave-uniform offset; padding reads the zeros stored there.
+template <typename T, int MS, int NSUB, int NV, bool TL>
 __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
   constexpr int E = ElemTraits<T>::E;
   constexpr int KSTEP = 4 * E;         // k-values of one step: one vector per lane group
@@ -104,11 +107,13 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
   const int k1 = min(a.K, k0 + a.kper);
   // Buffer loads over the workgroup's own rows: rows past M or N are past the
   // buffer's end and read zero, so a row costs no branch.
-  const int mrows = min(a.M - m0, 16 * MS);
-  const rsrc_t W = make_rsrc(reinterpret_cast<const T*>(a.W) + (size_t)nb * a.K,
-                             (unsigned)min(a.N - nb, 16 * NSUB) * (unsigned)a.K * (unsigned)sizeof(T));
-  const rsrc_t X = make_rsrc(reinterpret_cast<const T*>(a.X) + (size_t)m0 * a.ldx,
-                             ((unsigned)(mrows - 1) * (unsigned)a.ldx + (unsigned)a.K) * (unsigned)sizeof(T));
+  const rsrc_t W = TL ? make_rsrc(reinterpret_cast<const T*>(a.W) + (size_t)(nb >> 4) * a.wt * (16 * KSTEP),
+                                  (unsigned)min((a.N - nb + 15) >> 4, NSUB) * (unsigned)a.wt * 1024u)
+                      : make_rsrc(reinterpret_cast<const T*>(a.W) + (size_t)nb * a.K,
+                                  (unsigned)min(a.N - nb, 16 * NSUB) * (unsigned)a.K * (unsigned)sizeof(T));
+  const rsrc_t X = TL ? make_rsrc(a.X, (unsigned)a.wt * (unsigned)a.xt * 64u)
+                      : make_rsrc(reinterpret_cast<const T*>(a.X) + (size_t)m0 * a.ldx,
+                                  ((unsigned)(min(a.M - m0, 16 * MS) - 1) * (unsigned)a.ldx + (unsigned)a.K) * (unsigned)sizeof(T));
 
   f32x4 acc[MS][NSUB];
 #pragma unroll
@@ -122,6 +127,24 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
   for (int kr = k0 + wave * NV * KSTEP; kr < k1; kr += WKS * NV * KSTEP) {
     uint4 wreg[NSUB][NV], xreg[MS][NV];
     const int kl = kr + g4 * E;
+    if constexpr (TL) {
+      // a step past the range (the last wave's) loads zeros from past the
+      // buffer's end, and no row of X past the padded ones is read
+      const unsigned lo = (unsigned)(r16 * 64 + g4 * 16), kb = (unsigned)(kr / KSTEP), ke = (unsigned)((k1 + KSTEP - 1) / KSTEP);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const unsigned lv = kb + v < ke ? lo : kOob;
+#pragma unroll
+        for (int s = 0; s < NSUB; ++s) wreg[s][v] = buf_ld16(W, lv, ((unsigned)(s * a.wt) + kb + v) * 1024u);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        const bool ok = kb + v < ke;
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+          xreg[ms][v] = buf_ld16(X, ok && m0 + ms * 16 < a.xt ? lo : kOob, ((kb + v) * (unsigned)a.xt + (unsigned)(m0 + ms * 16)) * 64u);
+      }
+    } else {
     unsigned wo[NSUB], xo[MS];
 #pragma unroll
     for (int s = 0; s < NSUB; ++s) wo[s] = (unsigned)((s * 16 + r16) * a.K + kl) * (unsigned)sizeof(T);
@@ -135,7 +158,7 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
 #pragma unroll
       for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
-        for (int v = 0; v < NV; ++v) xreg[ms][v] = (ms == 0 || ms * 16 < mrows) ? buf_ld16(X, xo[ms] + 64u * v) : make_uint4(0, 0, 0, 0);
+        for (int v = 0; v < NV; ++v) xreg[ms][v] = buf_ld16(X, xo[ms] + 64u * v);
     } else {   // the range's end: vectors past it read zero
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
@@ -146,6 +169,8 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) xreg[ms][v] = buf_ld16(X, kl + v * KSTEP < k1 ? xo[ms] + 64u * v : kOob);
     }
+    }
+    __builtin_amdgcn_sched_barrier(0);   // every load of the round in flight before the first MFMA
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
@@ -208,7 +233,8 @@ __global__ __launch_bounds__(256) void gemm_wide(GemmArgs a) {
 #pragma unroll
         for (int v = 0; v < VPL; ++v) {
           const int k = k0 + c * KC + g4 * KCL + v * E;
-          wreg[s][c][v] = (n < N && k < K) ? ldg16(W + (size_t)n * K + k) : make_uint4(0, 0, 0, 0);
+          wreg[s][c][v] = (n < N && k < K) ? ldg16(W + (a.wt ? wtile_off<T>(n, k, a.wt) : (size_t)n * K + k))
+                                           : make_uint4(0, 0, 0, 0);
         }
     }
     if (k0 > 0) __syncthreads();  // previous slice's LDS reads done
@@ -588,13 +614,17 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
       src[i] = reinterpret_cast<const bf16_t*>(a.X) + (size_t)m * a.ldx + k0 + chunk * 8;
     } else {
       const int n = min(n0 + row - BM, N - 1);
-      src[i] = reinterpret_cast<const bf16_t*>(a.W) + (size_t)n * K + k0 + chunk * 8;
+      src[i] = reinterpret_cast<const bf16_t*>(a.W) +
+               (a.wt ? wtile_off<bf16_t>(n, k0 + chunk * 8, a.wt) : (size_t)n * K + k0 + chunk * 8);
     }
   }
+  static_assert(BM % (NWV * 8) == 0, "a load instruction holds X rows or W rows");
+  const int wstep = a.wt ? 1024 : 64;   // elements of a W row block per slice: two 16 x 32 tiles, or 64 columns
   auto issue = [&](auto j, int sl) {
     v4u* b = stage(j);
 #pragma unroll
-    for (int i = 0; i < LPT; ++i) dma16(src[i] + sl * 64, b + (i * NWV + wave) * 64);
+    for (int i = 0; i < LPT; ++i)
+      dma16(src[i] + sl * (i * NWV * 8 < BM ? 64 : wstep), b + (i * NWV + wave) * 64);
   };
 
   f32x4 acc[MSW][NSW];
@@ -695,17 +725,21 @@ hipError_t set_lds_attr(K_ kernel) {
                              160 * 1024);
 }
 
-template <typename T, int MS, int NSUB, int NV>
-hipError_t launch_skinny_t(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
+template <typename T, int MS, int NSUB, int NV, bool TL>
+hipError_t launch_skinny_l(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
-    hipError_t e = set_lds_attr(&gemm_skinny<T, MS, NSUB, NV>);
+    hipError_t e = set_lds_attr(&gemm_skinny<T, MS, NSUB, NV, TL>);
     if (e != hipSuccess) return e;
     attr = true;
   }
   const dim3 grid(8, sh.m_tiles, (sh.n_tiles * sh.nsplit + 7) / 8);
-  hipLaunchKernelGGL((gemm_skinny<T, MS, NSUB, NV>), grid, dim3(64 * WKS), sh.lds, s, a);
+  hipLaunchKernelGGL((gemm_skinny<T, MS, NSUB, NV, TL>), grid, dim3(64 * WKS), sh.lds, s, a);
   return hipGetLastError();
+}
+template <typename T, int MS, int NSUB, int NV>
+hipError_t launch_skinny_t(const SkinnyShape& sh, const GemmArgs& a, hipStream_t s) {
+  return a.wt ? launch_skinny_l<T, MS, NSUB, NV, true>(sh, a, s) : launch_skinny_l<T, MS, NSUB, NV, false>(sh, a, s);
 }
 
 template <typename T, int MS, int NSUB>
@@ -841,7 +875,7 @@ void skinny_shape(int et, int M, int N, int K, int ms, int nsub, int nsplit, Ski
 }
 
 bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh) {
-  if (M > 128) return false;
+  if (M > kSkinnyRows) return false;
   const int es = et == ET_BF16 ? 2 : 4, steps = cdiv_i(K, gemm_chunk_k(et) / VPL);
   double best = 1e30;
   for (int ms = 1; ms <= 4; ms *= 2) {
@@ -882,6 +916,7 @@ void wide_plan(int et, int M, int N, int K, int nsub, WideShape* sh) {
 
 hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStream_t s) {
   if (sh.units <= 0) return hipSuccess;
+  if ((a.wt != 0) != (a.xt != 0)) return hipErrorInvalidValue;   // both operands tiled, or neither
   a.n_tiles = sh.n_tiles;
   a.nsplit = sh.nsplit;
   a.split_log2 = sh.split_log2;
@@ -891,6 +926,7 @@ hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStre
 
 hipError_t launch_gemm_wide(int et, const WideShape& sh, GemmArgs a, hipStream_t s) {
   if (sh.units <= 0) return hipSuccess;
+  if (a.xt) return hipErrorInvalidValue;
   a.n_tiles = sh.n_tiles;
   a.nsplit = 1;
   return et == ET_BF16 ? wide_t<bf16_t>(sh, a, s) : wide_t<float>(sh, a, s);
@@ -941,6 +977,8 @@ hipError_t launch_gemm_tile(const TileShape& sh, GemmArgs a, hipStream_t s) {
   a.m_tiles = sh.m_tiles;
   a.nsplit = sh.nsplit;
   a.kper = sh.kper;
+  // tiled W: whole 64-wide slices (the ring kernel); X is row-major here
+  if (a.xt || a.ot || (a.wt && a.K % 64)) return hipErrorInvalidValue;
   switch (sh.ms * 10 + sh.ns) {
     case 24: return launch_tile_t<2, 4>(sh, a, s);
     case 44: return launch_tile_t<4, 4>(sh, a, s);

@@ -97,6 +97,7 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
   const int t = threadIdx.x;
   __shared__ float red[4];
   const float inv_d = 1.0f / (float)d;
+  const int ldu = a.ldu ? a.ldu : d;
   float4 xv[CPT], gg[CPT], bb[CPT];
   float ss = 0.0f;
   auto load_gb = [&]() {
@@ -230,11 +231,11 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
     const float u1 = xv[i].y * rstd * (1.0f + g.y) + b.y;
     const float u2 = xv[i].z * rstd * (1.0f + g.z) + b.z;
     const float u3 = xv[i].w * rstd * (1.0f + g.w) + b.w;
+    const size_t uo = act_off<T>(m, c, ldu, a.u_rows);
     if (sizeof(T) == 4 || a.u_f32) {
-      *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.u) + (size_t)m * d + c) = make_float4(u0, u1, u2, u3);
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.u) + uo) = make_float4(u0, u1, u2, u3);
     } else {
-      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.u) + (size_t)m * d + c) =
-          make_uint2(pack_bf16x2(u0, u1), pack_bf16x2(u2, u3));
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(a.u) + uo) = make_uint2(pack_bf16x2(u0, u1), pack_bf16x2(u2, u3));
     }
     xv[i] = make_float4(u0, u1, u2, u3);  // keep u for the quantiser
   }
@@ -279,6 +280,22 @@ hipError_t row_norm_cpt(const RowNormArgs& a, hipStream_t s) {
 template <typename T>
 hipError_t row_norm_mode(const RowNormArgs& a, hipStream_t s) {
   return a.mode == 0 ? row_norm_cpt<T, 0>(a, s) : a.mode == 1 ? row_norm_cpt<T, 1>(a, s) : row_norm_cpt<T, 2>(a, s);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void retile_kernel(T* dst, const T* src, int N, int K, int ktiles) {
+  constexpr int E = ElemTraits<T>::E, KS = 4 * E;
+  const size_t total = (size_t)((N + 15) / 16) * ktiles * 16 * 4;   // 16-byte vectors of dst
+  for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
+    const int v = (int)(i & 3), r = (int)((i >> 2) & 15);
+    const size_t b = i >> 6;
+    const int n = (int)(b / ktiles) * 16 + r, k = (int)(b % ktiles) * KS + v * E;
+    T e[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) e[j] = (n < N && k + j < K) ? src[(size_t)n * K + k + j] : T(0);
+#pragma unroll
+    for (int j = 0; j < E; ++j) dst[i * E + j] = e[j];
+  }
 }
 
 __global__ void copy_f32_kernel(float* dst, const float* src, size_t n) {
@@ -446,6 +463,19 @@ hipError_t launch_row_norm(int et, const RowNormArgs& a, hipStream_t s) {
 
 hipError_t launch_time_embed(int et, const CallParams* cp, void* e, int T, int Tpad, int d, hipStream_t s) {
   return launch_chunk_start(et, cp, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, d, e, T, Tpad, s);
+}
+
+hipError_t launch_retile(int et, void* dst, const void* src, int N, int K, int ktiles, hipStream_t s) {
+  const size_t total = (size_t)((N + 15) / 16) * ktiles * 64;
+  if (total == 0) return hipSuccess;
+  const dim3 grid((unsigned)(total / 256 + 1 > 8192 ? 8192 : total / 256 + 1));
+  if (et == ET_BF16)
+    hipLaunchKernelGGL(retile_kernel<bf16_t>, grid, dim3(256), 0, s, reinterpret_cast<bf16_t*>(dst),
+                       reinterpret_cast<const bf16_t*>(src), N, K, ktiles);
+  else
+    hipLaunchKernelGGL(retile_kernel<float>, grid, dim3(256), 0, s, reinterpret_cast<float*>(dst),
+                       reinterpret_cast<const float*>(src), N, K, ktiles);
+  return hipGetLastError();
 }
 
 hipError_t launch_copy_f32(float* dst, const float* src, size_t n, hipStream_t s) {

@@ -195,9 +195,9 @@ struct WTile {
   uint4 w[CPW][NS][VPL];
 };
 
-// W: [rows][ldw] bf16 (rsrc over the matrix), columns kofs + k; wrow[s] < 0: tile s absent.
+// W: tiled [rows / 16][K / 32][16][32] bf16 (rsrc over the matrix); wrow[s] < 0: tile s absent.
 template <int NS>
-VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int ldw, int kofs, int K, const int (&wrow)[NS]) {
+VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int K, const int (&wrow)[NS]) {
   // the wave index in a scalar register: the row-block offsets derived from it
   // are scalar, so each load is one instruction (no loop over lane values)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -205,13 +205,13 @@ VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int ldw, int kofs, int K, const 
 #pragma unroll
   for (int j = 0; j < CPW; ++j) {
     const int kc = 128 * (wave + NW * j);
-    const unsigned vb = (unsigned)(r16 * ldw + kofs + kc + 8 * g4) * 2u;
+    const unsigned vb = (unsigned)(r16 * 64 + g4 * 16);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bool on = kc < K && wrow[s] >= 0;
-      const unsigned sb = on ? (unsigned)wrow[s] * (unsigned)ldw * 2u : 0u;
+      const unsigned sb = on ? ((unsigned)(wrow[s] >> 4) * (unsigned)(K >> 5) + (unsigned)(kc >> 5)) * 1024u : 0u;
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) t.w[j][s][v] = on ? bld16(W, vb + 64u * v, sb, 0) : make_uint4(0, 0, 0, 0);
+      for (int v = 0; v < VPL; ++v) t.w[j][s][v] = on ? bld16(W, vb + 1024u * v, sb, 0) : make_uint4(0, 0, 0, 0);
     }
   }
 }
@@ -378,7 +378,7 @@ size_t lds_main(int hd) {
 // its own), each switched by an argument.  A form of its own, so that the
 // plain expert's kernel, which uses nearly every register, carries none of it;
 // always unfolded (the pi0-shaped state token makes 51 rows).  A pi0-shaped
-// chunk with all three over 571 prefix rows: 6.26 ms, against 10.5 ms as
+// chunk with all three over 571 prefix rows: 6.11 ms, against 10.5 ms as
 // about 1640 launches of a graph.
 template <int HD, int DPT, bool FOLD, bool VAR>
 __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
@@ -783,13 +783,13 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   constexpr int WOFF = 64 * (256 + 8) * 2;   // past the largest activation tile
   auto prefetch_wo = [&](int l) {
     const u32x4_t rs = rsrc_words(lt[l].wo, (unsigned)((size_t)d * dq * 2));
-    const unsigned vb = (unsigned)(r16 * dq + team * HTD + 8 * g4) * 2u;
+    const unsigned vb = (unsigned)(r16 * 64 + g4 * 16);
 #pragma unroll
     for (int i = 0; i < OTW * OKS / NW; ++i) {
       const int b = wave + NW * i, t = b / OKS, ks = b - t * OKS;
       const bool on = 16 * t < CW && 32 * ks < HTD;
-      const unsigned so = on ? (unsigned)(rank * CW + 16 * t) * (unsigned)dq * 2u : 0x7ffffff0u;
-      dma_x16_ro(rs, vb + 64u * ks, so, smem, (unsigned)(WOFF + b * 1024));
+      const unsigned so = ((unsigned)(rank * CW / 16 + t) * (unsigned)(dq >> 5) + (unsigned)(team * HTD / 32 + ks)) * 1024u;
+      dma_x16_ro(rs, on ? vb : 0x7ffffff0u, on ? so : 0u, smem, (unsigned)(WOFF + b * 1024));
     }
   };
 
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   {
     int wr[2], oc[2];
     qkv_rows(wr, oc);
-    prefetch_w<2>(wq, mkr(lt[0].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, 0, d, wr);
+    prefetch_w<2>(wq, mkr(lt[0].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
   }
   embed();
   norm_store(gam(0, 0, 0), gam(0, 0, 0) + d);
@@ -1137,7 +1137,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         gu_rows(wr);
-        prefetch_w<2>(wg, mkr(ly.wgu, (size_t)(a.glu ? 2 : 1) * a.F * d * 2), d, 0, d, wr);
+        prefetch_w<2>(wg, mkr(ly.wgu, (size_t)(a.glu ? 2 : 1) * a.F * d * 2), d, wr);
       }
       if (!wait_flags<true>(sy, team, &flag, pk3)) return bail();
       mark();
@@ -1194,7 +1194,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         dn_rows(wr);
-        prefetch_w<2>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, 0, F8, wr);
+        prefetch_w<2>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
       }
       if (!wait_flags<false>(sy, team, &flag, pk4)) return bail();
       mark();
@@ -1227,7 +1227,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         int wr[2], oc[2];
         qkv_rows(wr, oc);
         const int nl = last_layer ? 0 : l + 1;
-        prefetch_w<2>(wq, mkr(lt[nl].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, 0, d, wr);
+        prefetch_w<2>(wq, mkr(lt[nl].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
       }
       if (!wait_flags<true>(sy, team, &flag, pk5)) return bail();
       mark();
@@ -1269,7 +1269,8 @@ bool persist_supported(int d, int hd, int H, int G, int F, int n, int P, int A, 
   const int QT = (n + 15) / 16;
   if (HT * QT > NW) return false;            // attention: one wave per (head, query tile)
   if ((HT + 2) * hd / 16 > 2 * TSIZE) return false;  // QKV tiles: two per rank
-  if (F % 128 != 0 || F / 8 > 1024 || F / 128 > TSIZE) return false;  // h groups: one per rank
+  // h groups: one per rank; a team's F / 8 columns in whole 32-wide k-steps
+  if (F % 256 != 0 || F / 8 > 1024 || F / 128 > TSIZE) return false;
   (void)glu;
   if (A < 1 || A > 32) return false;         // head and embedding registers
   const int nbp = (P + 31) / 32, nbs = (n + 31) / 32;   // prefix and chunk-token key blocks

@@ -107,6 +107,7 @@ struct SubW {
   int kind = K_MLP;
   int cache_idx = -1;
   // dense (element type)
+  // matrices of an expert are tiled (device_common.h), those of a backbone row-major
   void* qkv = nullptr;  // [n_qkv][d]: W_q | W_k | W_v (self/joint) or W_q (cross)
   int n_qkv = 0;
   void* kvc = nullptr;  // [2 d_kv][d_p]: W_kc | W_vc
@@ -129,6 +130,7 @@ struct vla_model {
   int d = 0, dq = 0, dkv = 0, ns = 0, Lc = 0;
   std::vector<void*> allocs;
   void *W_in = nullptr, *W_s = nullptr, *E_pos = nullptr, *W_out = nullptr;
+  void* W_out_t = nullptr;  // dense models: W_out tiled
   void* kvc_all = nullptr;  // dense models: every cache slot's [W_kc | W_vc] stacked in slot order
   float *b_in = nullptr, *b_s = nullptr, *b_out = nullptr;
   void *W_t1 = nullptr, *W_t2 = nullptr, *W_fm = nullptr, *W_mod = nullptr;
@@ -501,13 +503,23 @@ vla_status build_plan(vla_model* m, Plan* p) {
   VLA_TRY(al((void**)&p->a, (size_t)B * n * A * 4));
   VLA_TRY(al((void**)&p->xs, (size_t)B * d * 4));
   VLA_TRY(al((void**)&p->x, (size_t)M * d * 4));
-  VLA_TRY(al(&p->u, (size_t)M * d * (u32 ? 4 : es)));
+  // Dense experts: projection inputs in whole slices of 64 columns (zeros past
+  // the width), tiled where the skinny kernel reads them, else row-major
+  const bool dense = !m->tern;
+  const int Mp = (M + 15) / 16 * 16, xt = dense && M <= kSkinnyRows ? Mp : 0;
+  const int ldu = dense ? kpad(d) : d, ldx_o = dense ? kpad(dq) : dq, ldh = dense ? kpad(F) : F;
+  VLA_TRY(al(&p->u, (size_t)Mp * ldu * (u32 ? 4 : es)));
   int ldqkv = 0;
   for (auto& lay : m->layers)
     for (auto& sw : lay) ldqkv = std::max(ldqkv, sw.n_qkv);
   VLA_TRY(al(&p->qkv, (size_t)M * ldqkv * es));
-  VLA_TRY(al(&p->o, (size_t)M * dq * es));
-  VLA_TRY(al(&p->h, (size_t)M * F * (m->tern ? 4 : es)));
+  VLA_TRY(al(&p->o, (size_t)Mp * ldx_o * es));
+  VLA_TRY(al(&p->h, (size_t)Mp * ldh * (m->tern ? 4 : es)));
+  if (dense) {
+    HIP_TRY(hipMemset(p->u, 0, (size_t)Mp * ldu * es));
+    HIP_TRY(hipMemset(p->o, 0, (size_t)Mp * ldx_o * es));
+    HIP_TRY(hipMemset(p->h, 0, (size_t)Mp * ldh * es));
+  }
   if (!c.head_regression) {
     VLA_TRY(al(&p->e, (size_t)T * d * es));
     VLA_TRY(al(&p->h1, (size_t)T * d * es));
@@ -578,8 +590,8 @@ vla_status build_plan(vla_model* m, Plan* p) {
     pa.eps = c.rms_eps;
     pa.scale = 1.0f / std::sqrt((float)hd);
     const size_t layer_block = (size_t)2 * B * c.n_kv_heads * P * hd;
-    // Team t reads only columns [t F / 8, (t + 1) F / 8) of W_d: one contiguous
-    // block per team instead of d pieces of F / 4 bytes, F * es bytes apart.
+    // Team t reads only columns [t F / 8, (t + 1) F / 8) of W_d: its k-tiles as
+    // one contiguous block instead of d / 16 pieces.
     if (m->wd_team.empty()) {
       Alloc am{m->allocs};
       const size_t F8 = (size_t)F / 8;
@@ -587,10 +599,12 @@ vla_status build_plan(vla_model* m, Plan* p) {
       for (int l = 0; l < L; ++l) {
         void* dst = nullptr;
         VLA_TRY(am(&dst, (size_t)d * F * es));
+        // k-tile (row block b, tile t) of the whole matrix -> team t / (F8 / 32)
         const char* src = static_cast<const char*>(m->layers[l][1].dn);
+        const size_t tb = F8 / 32 * 1024, rowb = (size_t)kpad(F) / 32 * 1024;
         for (int t = 0; t < 8; ++t)
-          HIP_TRY(hipMemcpy2D(static_cast<char*>(dst) + t * d * F8 * es, F8 * es, src + t * F8 * es, (size_t)F * es,
-                              F8 * es, d, hipMemcpyDeviceToDevice));
+          HIP_TRY(hipMemcpy2D(static_cast<char*>(dst) + t * d * F8 * es, tb, src + t * tb, rowb, tb, d / 16,
+                              hipMemcpyDeviceToDevice));
         wt[l] = dst;
       }
       HIP_TRY(hipDeviceSynchronize());
@@ -694,6 +708,14 @@ vla_status build_plan(vla_model* m, Plan* p) {
     return VLA_OK;
   }
 
+  // A projection of a dense expert from a padded input buffer
+  auto proj = [&](int N, int K, const void* X, const void* W) {
+    GemmArgs g = gemm_base(m, M, N, xt || et == ET_F32 ? K : kpad(K), X, kpad(K), W);
+    g.wt = kpad(K) / kstep(et);
+    g.xt = xt;
+    return g;
+  };
+
   // Residual projection (O or down) of a dense model: split-K partials summed
   // by the following row kernel (skinny), or the residual update in the
   // epilogue (wide).  Returns the partial count the row kernel must add.
@@ -749,6 +771,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
     RowNormArgs rn{};
     rn.mode = 1; rn.M = M; rn.d = d; rn.x = p->x; rn.a = p->a; rn.W_in = m->W_in; rn.xs = p->xs;
     rn.E_pos = m->E_pos; rn.n = nt; rn.stok = stok; rn.b_in = m->b_in; rn.A = A; rn.eps = c.rms_eps; rn.exact = m->tern; rn.u = p->u; rn.u_f32 = u32;
+    rn.ldu = ldu; rn.u_rows = xt;
     if (L > 0) {
       rn.gamma = modk;
       rn.beta = modk + d;
@@ -769,6 +792,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
         const float* alp = modk + ((size_t)l * ns + j) * 3 * d + 2 * d;
         RowNormArgs nr{};
         nr.mode = 0; nr.M = M; nr.d = d; nr.x = p->x; nr.eps = c.rms_eps; nr.exact = m->tern; nr.u = p->u; nr.u_f32 = u32;
+        nr.ldu = ldu; nr.u_rows = xt;
         next_gb(l, j, &nr.gamma, &nr.beta);
         // the head projection is dense: it reads u in the element type
         const bool last_sub = l == L - 1 && j == (int)subs.size() - 1;
@@ -781,13 +805,14 @@ vla_status build_plan(vla_model* m, Plan* p) {
           const bool glu = c.mlp != VLA_MLP_GELU;
           const int ngu = glu ? 2 * F : F;
           if (!m->tern) {
-            GemmArgs g = gemm_base(m, M, ngu, d, p->u, d, sw.gu);
+            GemmArgs g = proj(ngu, d, p->u, sw.gu);
             g.epi = glu ? EPI_GLU : EPI_STORE;
             g.act = mlp_act(c.mlp);
             g.out = p->h;
-            g.ldo = F;
+            g.ldo = ldh;
+            g.ot = xt;
             bld.gemm(g, glu ? 2 : 1);
-            resid_gemm(gemm_base(m, M, d, F, p->h, F, sw.dn), alp, nr);
+            resid_gemm(proj(d, F, p->h, sw.dn), alp, nr);
           } else {
             // u was quantised (q8, r8) by the row kernel that wrote it
             QuantArgs q{};
@@ -814,7 +839,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
           }
         } else {
           if (!m->tern) {
-            GemmArgs g = gemm_base(m, M, sw.n_qkv, d, p->u, d, sw.qkv);
+            GemmArgs g = proj(sw.n_qkv, d, p->u, sw.qkv);
             g.epi = EPI_STORE;
             g.out = p->qkv;
             g.ldo = ldqkv;
@@ -854,11 +879,12 @@ vla_status build_plan(vla_model* m, Plan* p) {
           at.cp = cp;
           at.layer_off = sw.cache_idx >= 0 ? (size_t)sw.cache_idx * layer_block : 0;
           at.o = p->o;
-          at.ldo = dq;
+          at.ldo = ldx_o;
+          at.o_rows = xt;
           at.scale = 1.0f / std::sqrt((float)hd);
           bld.attn(at);
           if (!m->tern) {
-            resid_gemm(gemm_base(m, M, d, dq, p->o, dq, sw.o), alp, nr);
+            resid_gemm(proj(d, dq, p->o, sw.o), alp, nr);
           } else {
             QuantArgs q{};
             q.M = M; q.K = dq; q.x = p->o; q.ldx = dq; q.src_type = 1; q.q = p->q8; q.r = p->r8;
@@ -885,7 +911,7 @@ vla_status build_plan(vla_model* m, Plan* p) {
       }
     }
     // head: out-projection of the finally-normalised stream and the Euler update
-    GemmArgs g = gemm_base(m, M, A, d, p->u, d, m->W_out);
+    GemmArgs g = dense ? proj(A, d, p->u, m->W_out_t) : gemm_base(m, M, A, d, p->u, d, m->W_out);
     g.epi = EPI_EULER;
     g.bias = m->b_out;
     g.a = p->a;
@@ -1095,6 +1121,15 @@ vla_status upload_scales(vla_model* m, float** dst, const std::vector<float>& v)
   return VLA_OK;
 }
 
+// A tiled copy of a row-major dense matrix [N][K] in library memory.
+vla_status tile_matrix(vla_model* m, void** dst, const void* src, int N, int K) {
+  Alloc al{m->allocs};
+  const int kt = kpad(K) / kstep(m->et);
+  VLA_TRY(al(dst, (size_t)((N + 15) / 16) * kt * 1024));
+  HIP_TRY(launch_retile(m->et, *dst, src, N, K, kt, nullptr));
+  return VLA_OK;
+}
+
 // A group of matrices fused along rows: dense or packed.
 struct Part {
   const void* src;
@@ -1102,13 +1137,16 @@ struct Part {
   float scale;
 };
 
-vla_status fuse(vla_model* m, void** dst, float** scales, const std::vector<Part>& parts, int K, bool interleave) {
+// tile: a dense matrix of an expert, stored tiled with K padded to whole slices.
+vla_status fuse(vla_model* m, void** dst, float** scales, const std::vector<Part>& parts, int K, bool interleave,
+                bool tile = false) {
   const bool tern = m->tern;
   const size_t rowbytes = tern ? (size_t)K / 4 : (size_t)K * esize(m->et);
   int rows = 0;
   for (auto& p : parts) rows += p.rows;
   Alloc al{m->allocs};
   VLA_TRY(al(dst, (size_t)rows * rowbytes));
+  const size_t at = m->allocs.size() - 1;
   std::vector<float> sc;
   if (interleave) {
     // two parts of equal rows: blocks of 16 rows alternate between them
@@ -1128,6 +1166,13 @@ vla_status fuse(vla_model* m, void** dst, float** scales, const std::vector<Part
   }
   if (tern) HIP_TRY(launch_ternary_repack(*dst, (size_t)rows * rowbytes, nullptr));
   if (tern && scales) VLA_TRY(upload_scales(m, scales, sc));
+  if (tile && !tern) {
+    void* rm = *dst;
+    VLA_TRY(tile_matrix(m, dst, rm, rows, K));
+    HIP_TRY(hipDeviceSynchronize());
+    (void)hipFree(rm);
+    m->allocs.erase(m->allocs.begin() + (long)at);
+  }
   return VLA_OK;
 }
 
@@ -1169,6 +1214,7 @@ vla_status create_impl(const vla_config* cfg, const void* const* weights, int32_
     VLA_TRY(tr.next(&p, "b_fm")); VLA_TRY(copy_in(m.get(), (void**)&m->b_fm, p, (size_t)2 * d * 4));
   }
   VLA_TRY(tr.next(&p, "W_out")); VLA_TRY(copy_in(m.get(), &m->W_out, p, (size_t)A * d * es));
+  if (!m->tern) VLA_TRY(tile_matrix(m.get(), &m->W_out_t, m->W_out, A, d));
   VLA_TRY(tr.next(&p, "b_out")); VLA_TRY(copy_in(m.get(), (void**)&m->b_out, p, (size_t)A * 4));
 
   const size_t modrow = (size_t)3 * ns * d;
@@ -1213,16 +1259,16 @@ vla_status create_impl(const vla_config* cfg, const void* const* weights, int32_
           float s1, s2;
           VLA_TRY(mat("W1", &w1, &s1));
           VLA_TRY(mat("W2", &w2, &s2));
-          VLA_TRY(fuse(m.get(), &sw.gu, &sw.s_gu, {{w1, F, s1}}, d, false));
-          VLA_TRY(fuse(m.get(), &sw.dn, &sw.s_dn, {{w2, d, s2}}, F, false));
+          VLA_TRY(fuse(m.get(), &sw.gu, &sw.s_gu, {{w1, F, s1}}, d, false, true));
+          VLA_TRY(fuse(m.get(), &sw.dn, &sw.s_dn, {{w2, d, s2}}, F, false, true));
         } else {
           const void *wg, *wu, *wd;
           float sg, su, sd;
           VLA_TRY(mat("W_g", &wg, &sg));
           VLA_TRY(mat("W_u", &wu, &su));
           VLA_TRY(mat("W_d", &wd, &sd));
-          VLA_TRY(fuse(m.get(), &sw.gu, &sw.s_gu, {{wg, F, sg}, {wu, F, su}}, d, true));
-          VLA_TRY(fuse(m.get(), &sw.dn, &sw.s_dn, {{wd, d, sd}}, F, false));
+          VLA_TRY(fuse(m.get(), &sw.gu, &sw.s_gu, {{wg, F, sg}, {wu, F, su}}, d, true, true));
+          VLA_TRY(fuse(m.get(), &sw.dn, &sw.s_dn, {{wd, d, sd}}, F, false, true));
         }
       } else {
         const void *wq, *wk = nullptr, *wv = nullptr, *wkc = nullptr, *wvc = nullptr, *wo;
@@ -1243,12 +1289,12 @@ vla_status create_impl(const vla_config* cfg, const void* const* weights, int32_
           qkv.push_back({wv, dkv, sv});
         }
         sw.n_qkv = has_self(k) ? dq + 2 * dkv : dq;
-        VLA_TRY(fuse(m.get(), &sw.qkv, &sw.s_qkv, qkv, d, false));
+        VLA_TRY(fuse(m.get(), &sw.qkv, &sw.s_qkv, qkv, d, false, true));
         if (has_prefix(k)) {
           VLA_TRY(fuse(m.get(), &sw.kvc, &sw.s_kvc, {{wkc, dkv, skc}, {wvc, dkv, svc}}, dp, false));
           sw.cache_idx = cidx++;
         }
-        VLA_TRY(fuse(m.get(), &sw.o, &sw.s_o, {{wo, d, so}}, dq, false));
+        VLA_TRY(fuse(m.get(), &sw.o, &sw.s_o, {{wo, d, so}}, dq, false, true));
       }
       m->layers[l].push_back(sw);
     }
@@ -1611,8 +1657,8 @@ int32_t vla_test_persist_trace(vla_model* m, uint64_t* out, int32_t max_per_team
 vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, int32_t N, int32_t K,
                          int32_t variant, float* y, void* stream) {
   if (elem != 0 && elem != 1) return fail(VLA_E_ARG, "elem must be 0 or 1");
-  if (variant < 0 || (variant > 4 && variant < 10) || variant > 14)
-    return fail(VLA_E_ARG, "variant must be 0..4 or 10..14");
+  if (variant < 0 || (variant > 4 && variant < 10) || (variant > 14 && variant < 20) || variant > 21)
+    return fail(VLA_E_ARG, "variant must be 0..4, 10..14, 20 or 21");
   if (!x || !w || !y || !al16(x) || !al16(w) || !al16(y)) return fail(VLA_E_ARG, "bad buffer");
   if (M < 1 || N < 1 || K < 1 || K % (elem ? 8 : 4)) return fail(VLA_E_SHAPE, "bad GEMM shape");
   const int et = elem ? ET_BF16 : ET_F32;
@@ -1620,6 +1666,37 @@ vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, 
   GemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.X = x; g.ldx = K; g.W = w;
   g.epi = EPI_STORE; g.out = y; g.ldo = N; g.out_f32 = 1;
+  struct Bufs {   // operands of variants 20 and 21, in an expert's layouts
+    void *x = nullptr, *w = nullptr;
+    ~Bufs() {
+      (void)hipFree(x);
+      (void)hipFree(w);
+    }
+  } bufs;
+  if (variant >= 20) {
+    const int ks = kstep(et), Kp = kpad(K), kt = Kp / ks, Mp = (M + 15) / 16 * 16;
+    const size_t es = esize(et);
+    if (hipMalloc(&bufs.x, (size_t)Mp * Kp * es) != hipSuccess ||
+        hipMalloc(&bufs.w, (size_t)((N + 15) / 16) * kt * 1024) != hipSuccess)
+      return fail(VLA_E_NOMEM, "gemm operands");
+    HIP_TRY(hipMemset(bufs.x, 0, (size_t)Mp * Kp * es));
+    HIP_TRY(launch_retile(et, bufs.w, w, N, K, kt, nullptr));
+    g.W = bufs.w;
+    g.wt = kt;
+    g.X = bufs.x;
+    g.ldx = Kp;
+    if (M <= kSkinnyRows) {
+      g.xt = Mp;
+      for (int t = 0; t * ks < K; ++t)
+        HIP_TRY(hipMemcpy2D((char*)bufs.x + (size_t)t * Mp * 64, 64, (const char*)x + (size_t)t * 64, K * es,
+                            std::min(ks, K - t * ks) * es, M, hipMemcpyDeviceToDevice));
+    } else {
+      if (et == ET_BF16) g.K = Kp;
+      HIP_TRY(hipMemcpy2D(bufs.x, Kp * es, x, K * es, K * es, M, hipMemcpyDeviceToDevice));
+    }
+    HIP_TRY(hipDeviceSynchronize());
+    variant = variant == 21 ? 4 : 0;
+  }
   if (variant == 4) {
     // the residual projections' launch: split-K fp32 partials, summed here
     g.epi = EPI_PARTIAL;

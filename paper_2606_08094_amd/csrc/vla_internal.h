@@ -38,7 +38,10 @@ struct GemmArgs {
   int M, N, K;
   const void* X;
   int ldx;
-  const void* W;           // [N][K] row-major in the element type
+  const void* W;           // [N][K] row-major in the element type, or tiled (wt)
+  int wt;                  // k-tiles of a 16-row block when W is tiled (64-byte k-steps, see xtile_off), 0 = row-major
+  int xt;                  // padded rows of X when it is tiled (skinny kernel), 0 = row-major
+  int ot;                  // padded rows of out when the epilogue writes it tiled (skinny kernel), 0 = row-major
   int n_tiles;             // tiles along N (set by the launcher)
   int m_tiles;             // tiles along M (tiled kernel; set by the launcher)
   int nsplit;              // K-splits (set by the launcher; > 1 only with EPI_PARTIAL)
@@ -82,8 +85,9 @@ struct AttnArgs {
   const void* vc;
   const CallParams* cp;    // kv_cache base when kc == NULL
   size_t layer_off;        // element offset of this layer's K block in the cache
-  void* o;                 // [B*n][ldo]
+  void* o;                 // [B*n][ldo], or tiled with o_rows padded rows
   int ldo;
+  int o_rows;              // 0 = row-major
   float scale;
   int kv_split;            // key splits
   int hsplit;              // groups of query heads per K/V head (workgroups per group)
@@ -127,7 +131,9 @@ struct RowNormArgs {
   const float* beta;
   float eps;
   int exact;               // 1 (W2A8 models): 1 / sqrt by correctly rounded steps
-  void* u;                 // [M][d] element type (u_f32 = 0) or fp32
+  void* u;                 // [M][ldu] element type (u_f32 = 0) or fp32
+  int ldu;                 // 0 = d
+  int u_rows;              // u (element type) tiled with this many padded rows, 0 = row-major
   int u_f32;
   int8_t* q;               // if set (u_f32 = 1): also the int8 absmax quantisation of u, [M][d]
   float* qr;               // and its per-row absmax [M]
@@ -167,6 +173,7 @@ struct TileShape {
 // Persistent tensor-parallel denoise loop (bf16, joint attention, batch 1):
 // weights of one layer, library-owned.
 struct PLayer {
+  // all tiled ([rows / 16][columns / 32][16][32])
   const void* wqkv;          // [d_q + 2 d_kv][d]
   const void* wo;            // [d][d_q]
   const void* wgu;           // GLU: gate/up interleaved in 16-row blocks [2F][d]; GELU: W1 [F][d]
@@ -224,7 +231,15 @@ constexpr int PERSIST_TRACE_MAX = 8192;
 constexpr int PERSIST_TRACE_WG = 8 * PERSIST_TRACE_MAX / 256;   // marks per workgroup when all record
 constexpr int PERSIST_MAX_LAYERS = 64;
 
+// Values of one 64-byte k-step, and a reduction length padded to whole slices
+// of every dense kernel (64 values).
+constexpr int kSkinnyRows = 128;   // most token rows of the skinny GEMM
+inline int kstep(int et) { return et == 1 ? 32 : 16; }
+inline int kpad(int k) { return (k + 63) / 64 * 64; }
+
 // ---- launchers (each enqueues on `s`, returns hipError_t) ----
+// dst [ceil(N / 16)][ktiles][16][kstep] from row-major src [N][K], zeros past N and K
+hipError_t launch_retile(int et, void* dst, const void* src, int N, int K, int ktiles, hipStream_t s);
 int gemm_chunk_k(int et);  // K covered by one chunk (all 4 lane groups of a wave)
 void skinny_shape(int et, int M, int N, int K, int ms, int nsub, int nsplit, SkinnyShape* sh);
 bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh);

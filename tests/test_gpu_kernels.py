@@ -78,6 +78,27 @@ def test_gemm_parity(torch, elem, M, N, K):
         assert np.all(err <= bound), f"variant={variant} max err {err.max()} worst ratio {(err / bound).max()}"
 
 
+@pytest.mark.parametrize("elem", [1, 0])
+@pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
+def test_gemm_tiled_operands(torch, elem, M, N, K):
+    """The projections on operands in the layouts of an expert's plans: 64-byte
+    k-steps of 16 rows as one kilobyte, zeros past the rows and past K."""
+    bf = elem == 1
+    seed = 1000 * M + N + K
+    x = wl.random_matrix((M, K), seed, 1.0, bf16=bf)
+    w = wl.random_matrix((N, K), seed + 1, 0.05, bf16=bf)
+    bound = _fp32_bound(x.astype(np.float64), w.astype(np.float64))
+    for variant in (20, 21):
+        y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        try:
+            _vla().test_gemm(elem, _dev(torch, x, bf), _dev(torch, w, bf), M, N, K, y, variant=variant)
+        except _vla().VlaError as e:
+            assert e.status == 3 and variant == 21 and not bf and M > 128, e
+            continue
+        err = np.abs(y.cpu().numpy().astype(np.float64) - O.linear(x, w))
+        assert np.all(err <= bound), f"variant={variant} max err {err.max()} worst ratio {(err / bound).max()}"
+
+
 ATTN_CASES = [
     # (elem, mode, B, n, P, H, G, hd)
     (1, 2, 1, 50, 816, 8, 1, 256),     # pi0 joint
