@@ -23,8 +23,7 @@ extern "C" {
  * split and tile), summed into y by the library (VLA_E_UNSUPPORTED for fp32
  * with M > 128; a temporary partial buffer is allocated and freed),
  * 20, 21 = variants 0 and 4 on operands in the layouts of an expert's plans
- * (weights tiled, x tiled up to 128 rows and padded to whole 64-wide slices
- * beyond; copies are made and freed),
+ * (both tiled, K padded to whole 64-wide slices; copies are made and freed),
  * 10..14 = the tiled kernel with tile 64x128, 128x128, 256x128, 128x256 or
  * 256x256 (eight waves; needs K % 64 == 0) (VLA_E_UNSUPPORTED unless bf16
  * with M > 128, and for 256x256 with K % 64 != 0). */

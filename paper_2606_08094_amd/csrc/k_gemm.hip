@@ -69,7 +69,7 @@ VLA_DEV void stage_x(const GemmArgs& a, T* xs, int pitch, int m0, int k0, int KW
       const int i = base + u * nthr;
       const int row = i / vrow, kv = i - row * vrow;
       const bool ok = i < total && (m0 + row) < a.M && (k0 + kv * E) < a.K;
-      v[u] = ok ? ldg16(X + (size_t)(m0 + row) * a.ldx + k0 + kv * E) : make_uint4(0, 0, 0, 0);
+      v[u] = ok ? ldg16(X + act_off<T>(m0 + row, k0 + kv * E, a.ldx, a.xt)) : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
@@ -264,163 +264,125 @@ __global__ __launch_bounds__(256) void gemm_wide(GemmArgs a) {
 constexpr int TBK = 64;           // K-slice of gemm_tile
 constexpr int TPITCH = TBK + 8;   // LDS row pitch in elements (16 bytes of padding)
 
-// LDS of gemm_tile_rs: two K-slice buffers of X and W rows, reused for the
-// fp32 output tile by the epilogue.
+// LDS of gemm_tile_rs: two K-slice buffers of X and W rows.
 template <int MS, int NS>
 constexpr size_t tile_lds_bytes() {
-  const size_t stage = (size_t)2 * (32 * MS + 32 * NS) * TPITCH * sizeof(bf16_t);
-  const size_t out = (size_t)(32 * MS) * (32 * NS + 4) * sizeof(float);
-  return stage > out ? stage : out;
+  return (size_t)2 * (32 * MS + 32 * NS) * TPITCH * sizeof(bf16_t);
 }
 
-
-// Epilogue of the tiled kernels over the fp32 tile ct [BM][CP] (rows m0..,
-// columns n0..): each thread finishes 4 consecutive columns of a row, so a row
-// is written with 8- or 16-byte stores.  For EPI_GLU the tile's columns are
-// 16-row blocks of gate and up rows in turn, and output column f pairs gate
-// column (f/16)*32 + f%16 with the up column 16 further on.
-VLA_DEV void store4(float* p, float4 v, bool vec) {
-  if (vec) *reinterpret_cast<float4*>(p) = v;
-  else { p[0] = v.x; p[1] = v.y; p[2] = v.z; p[3] = v.w; }
+// Epilogue of the tiled kernels, straight from the accumulators.  W is the
+// MFMA's row operand, so a lane holds four consecutive columns n of one token
+// row m (for EPI_GLU four of a gate and of its up subtile) and writes them
+// with one 8- or 16-byte store; a row's 16 columns are four lanes' stores.
+VLA_DEV void store4(float* p, f32x4 v, bool vec) {
+  if (vec) *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  else { p[0] = v[0]; p[1] = v[1]; p[2] = v[2]; p[3] = v[3]; }
 }
-VLA_DEV void store4(bf16_t* p, float4 v, bool vec) {
-  if (vec) *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
-  else { p[0] = f2bf(v.x); p[1] = f2bf(v.y); p[2] = f2bf(v.z); p[3] = f2bf(v.w); }
+VLA_DEV void store4(bf16_t* p, f32x4 v, bool vec) {
+  if (vec) *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+  else { p[0] = f2bf(v[0]); p[1] = f2bf(v[1]); p[2] = f2bf(v[2]); p[3] = f2bf(v[3]); }
 }
-// Columns c .. c+3 of which only the first `n` exist.
+// Columns n .. n+3 of which only the first `nv` exist.
 template <typename T>
-VLA_DEV void store4n(T* p, float4 v, int n, bool vec) {
-  if (n >= 4) { store4(p, v, vec); return; }
-  const float e[4] = {v.x, v.y, v.z, v.w};
-  for (int j = 0; j < n; ++j) {
-    if constexpr (sizeof(T) == 4) p[j] = e[j]; else p[j] = f2bf(e[j]);
+VLA_DEV void store4n(T* p, f32x4 v, int nv, bool vec) {
+  if (nv >= 4) { store4(p, v, vec); return; }
+  for (int j = 0; j < nv; ++j) {
+    if constexpr (sizeof(T) == 4) p[j] = v[j]; else p[j] = f2bf(v[j]);
   }
 }
-VLA_DEV float4 act4(int act, float4 v) { return make_float4(act_f(act, v.x), act_f(act, v.y), act_f(act, v.z), act_f(act, v.w)); }
+VLA_DEV f32x4 act4(int act, f32x4 v) { return f32x4{act_f(act, v[0]), act_f(act, v[1]), act_f(act, v[2]), act_f(act, v[3])}; }
 
-// Runs f(m, n, nv, v) for every 4-column group of the tile's first `rows`
-// rows (nv = columns left in the matrix from n, v = the tile's 4 values; for
-// GLU the 4 gate and 4 up values come as g and u).  The loop is unrolled with
-// every LDS read issued before the first store.
-template <int RP, int BN, int CP, int NT, typename Fn>
-VLA_DEV void epi_rows(const float* ct, int rows, int n0, int N, Fn&& f) {
-  constexpr int TPR = BN / 4, IT = (RP * TPR + NT - 1) / NT;
-  float4 v[IT];
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int idx = threadIdx.x + NT * j;
-    const int r = idx / TPR, c = (idx % TPR) * 4;
-    v[j] = (r < RP) ? *reinterpret_cast<const float4*>(ct + r * CP + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int idx = threadIdx.x + NT * j;
-    const int r = idx / TPR, c = (idx % TPR) * 4;
-    if (r < rows && n0 + c < N) f(r, n0 + c, N - (n0 + c), v[j]);
-  }
-}
-template <int RP, int BN, int CP, int NT, typename Fn>
-VLA_DEV void epi_rows_glu(const float* ct, int rows, int f0, int F, Fn&& f) {
-  constexpr int TPR = BN / 8, IT = (RP * TPR + NT - 1) / NT;
-  float4 g[IT], u[IT];
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int idx = threadIdx.x + NT * j;
-    const int r = idx / TPR, c = (idx % TPR) * 4;
-    const int cg = (c >> 4) * 32 + (c & 15);
-    g[j] = (r < RP) ? *reinterpret_cast<const float4*>(ct + r * CP + cg) : make_float4(0.f, 0.f, 0.f, 0.f);
-    u[j] = (r < RP) ? *reinterpret_cast<const float4*>(ct + r * CP + cg + 16) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int j = 0; j < IT; ++j) {
-    const int idx = threadIdx.x + NT * j;
-    const int r = idx / TPR, c = (idx % TPR) * 4;
-    if (r < rows && f0 + c < F) f(r, f0 + c, F - (f0 + c), g[j], u[j]);
-  }
-}
-
-template <int RP, int BN, int CP, int NT = 256>
-VLA_DEV void tile_epilogue(const GemmArgs& a, const float* ct, int m0, int n0, int split) {
+// acc[ms][ns]: rows mb + 16 ms + r16, columns nb + 16 ns + 4 g4 + i.
+template <int MSW, int NSW>
+VLA_DEV void tile_epilogue(const GemmArgs& a, const f32x4 (&acc)[MSW][NSW], int mb, int nb, int split) {
+  const int lane = threadIdx.x & 63, r16 = lane & 15, c0 = (lane >> 4) * 4;
   const int M = a.M, N = a.N;
-  const int rows = min(RP, M - m0);
-  if (rows <= 0) return;
+  // f(m, n, nv, v) for every 4-column group that exists
+  auto each = [&](auto&& f) {
+#pragma unroll
+    for (int ms = 0; ms < MSW; ++ms) {
+      const int m = mb + 16 * ms + r16;
+      if (m >= M) continue;
+#pragma unroll
+      for (int ns = 0; ns < NSW; ++ns) {
+        const int n = nb + 16 * ns + c0;
+        if (n < N) f(m, n, N - n, acc[ms][ns]);
+      }
+    }
+  };
   switch (a.epi) {
     case EPI_GLU: {
       const bool vec = (a.ldo & 3) == 0;
-      const int act = a.act;
-      auto f = [&](int r, int fc, int nv, float4 g, float4 u) {
-        const float4 gg = act4(act, g);
-        const float4 h = make_float4(gg.x * u.x, gg.y * u.y, gg.z * u.z, gg.w * u.w);
-        const size_t o = (size_t)(m0 + r) * a.ldo + fc;
-        if (a.out_f32) store4n(reinterpret_cast<float*>(a.out) + o, h, nv, vec);
-        else store4n(reinterpret_cast<bf16_t*>(a.out) + o, h, nv, vec);
-      };
-      epi_rows_glu<RP, BN, CP, NT>(ct, rows, n0 / 2, N / 2, f);
+      const int act = a.act, F = N / 2;
+#pragma unroll
+      for (int ms = 0; ms < MSW; ++ms) {
+        const int m = mb + 16 * ms + r16;
+        if (m >= M) continue;
+#pragma unroll
+        for (int j = 0; j < NSW / 2; ++j) {
+          const int fc = nb / 2 + 16 * j + c0;
+          if (fc >= F) continue;
+          const f32x4 h = act4(act, acc[ms][2 * j]) * acc[ms][2 * j + 1];
+          if (a.out_f32) store4n(reinterpret_cast<float*>(a.out) + (size_t)m * a.ldo + fc, h, F - fc, vec);
+          else store4n(reinterpret_cast<bf16_t*>(a.out) + act_off<bf16_t>(m, fc, a.ldo, a.ot), h, F - fc, vec);
+        }
+      }
       break;
     }
     case EPI_STORE: {
       const bool vec = (a.ldo & 3) == 0;
-      auto f = [&](int r, int n, int nv, float4 v) {
-        if (a.bias) {
-          const float b[4] = {a.bias[n], nv > 1 ? a.bias[n + 1] : 0.f, nv > 2 ? a.bias[n + 2] : 0.f,
-                              nv > 3 ? a.bias[n + 3] : 0.f};
-          v = make_float4(v.x + b[0], v.y + b[1], v.z + b[2], v.w + b[3]);
-        }
+      each([&](int m, int n, int nv, f32x4 v) {
+        if (a.bias)
+          v += f32x4{a.bias[n], nv > 1 ? a.bias[n + 1] : 0.f, nv > 2 ? a.bias[n + 2] : 0.f, nv > 3 ? a.bias[n + 3] : 0.f};
         v = act4(a.act, v);
-        const size_t o = (size_t)(m0 + r) * a.ldo + n;
-        if (a.out_f32) store4n(reinterpret_cast<float*>(a.out) + o, v, nv, vec);
-        else store4n(reinterpret_cast<bf16_t*>(a.out) + o, v, nv, vec);
-      };
-      epi_rows<RP, BN, CP, NT>(ct, rows, n0, N, f);
+        if (a.out_f32) store4n(reinterpret_cast<float*>(a.out) + (size_t)m * a.ldo + n, v, nv, vec);
+        else store4n(reinterpret_cast<bf16_t*>(a.out) + act_off<bf16_t>(m, n, a.ldo, a.ot), v, nv, vec);
+      });
       break;
     }
     case EPI_PARTIAL: {
       float* out = reinterpret_cast<float*>(a.out) + (size_t)split * M * a.ldo;
       const bool vec = (a.ldo & 3) == 0;
-      auto f = [&](int r, int n, int nv, float4 v) { store4n(out + (size_t)(m0 + r) * a.ldo + n, v, nv, vec); };
-      epi_rows<RP, BN, CP, NT>(ct, rows, n0, N, f);
+      each([&](int m, int n, int nv, f32x4 v) { store4n(out + (size_t)m * a.ldo + n, v, nv, vec); });
       break;
     }
     case EPI_RESID: {
-      auto f = [&](int r, int n, int nv, float4 v) {
-        float* xp = a.xres + (size_t)(m0 + r) * a.ldxr + n;
-        const float e[4] = {v.x, v.y, v.z, v.w};
-        for (int j = 0; j < 4 && j < nv; ++j) xp[j] = xp[j] + a.alpha[n + j] * e[j];
-      };
-      epi_rows<RP, BN, CP, NT>(ct, rows, n0, N, f);
+      const bool vec = (a.ldxr & 3) == 0;
+      each([&](int m, int n, int nv, f32x4 v) {
+        float* xp = a.xres + (size_t)m * a.ldxr + n;
+        if (vec && nv >= 4) {
+          const float4 x = *reinterpret_cast<const float4*>(xp), al = *reinterpret_cast<const float4*>(a.alpha + n);
+          *reinterpret_cast<float4*>(xp) = make_float4(x.x + al.x * v[0], x.y + al.y * v[1], x.z + al.z * v[2], x.w + al.w * v[3]);
+        } else {
+          for (int j = 0; j < 4 && j < nv; ++j) xp[j] = xp[j] + a.alpha[n + j] * v[j];
+        }
+      });
       break;
     }
     case EPI_KVCACHE: {
       const int G = a.d_kv / a.hd;
-      auto f = [&](int r, int n, int nv, float4 v) {
-        const int m = m0 + r;
+      each([&](int m, int n, int nv, f32x4 v) {
+        // hd, d_kv and lay_cols are multiples of 16: the four columns share a head's row
         const int b = m / a.P, p = m - b * a.P;
-        const float e[4] = {v.x, v.y, v.z, v.w};
-        for (int j = 0; j < 4 && j < nv; ++j) {
-          const int nn = n + j;
-          const int slot = a.lay_cols > 0 ? nn / a.lay_cols : 0;
-          const int nl = nn - slot * a.lay_cols;
-          const int kv = nl / a.d_kv, rem = nl - kv * a.d_kv;
-          const int g = rem / a.hd, cc = rem - g * a.hd;
-          const size_t o = (size_t)slot * a.lay_stride + ((((size_t)kv * a.B + b) * G + g) * a.P + p) * a.hd + cc;
-          reinterpret_cast<bf16_t*>(a.cache)[o] = f2bf(e[j]);
-        }
-      };
-      epi_rows<RP, BN, CP, NT>(ct, rows, n0, N, f);
+        const int slot = a.lay_cols > 0 ? n / a.lay_cols : 0;
+        const int nl = n - slot * a.lay_cols;
+        const int kv = nl / a.d_kv, rem = nl - kv * a.d_kv;
+        const int g = rem / a.hd, cc = rem - g * a.hd;
+        const size_t o = (size_t)slot * a.lay_stride + ((((size_t)kv * a.B + b) * G + g) * a.P + p) * a.hd + cc;
+        store4n(reinterpret_cast<bf16_t*>(a.cache) + o, v, nv, true);
+      });
       break;
     }
     case EPI_EULER: {
       const CallParams* cp = a.cp;
       const float dt = cp->tau[a.step + 1] - cp->tau[a.step];
-      auto f = [&](int r, int n, int nv, float4 v) {
-        const int m = m0 + r;
+      each([&](int m, int n, int nv, f32x4 v) {
         const int t = a.stok ? m % a.stok : 1;   // state-token rows: no action
         const int am = a.stok ? (m / a.stok) * (a.stok - 1) + t - 1 : m;
         if (t == 0) return;
-        const float e[4] = {v.x, v.y, v.z, v.w};
         for (int j = 0; j < 4 && j < nv; ++j) {
           const int nn = n + j;
-          const float vv = e[j] + a.bias[nn];
+          const float vv = v[j] + a.bias[nn];
           float* ap = a.a + (size_t)am * N + nn;
           const float an = a.regression ? vv : (*ap + dt * vv);
           *ap = an;
@@ -431,8 +393,7 @@ VLA_DEV void tile_epilogue(const GemmArgs& a, const float* ct, int m0, int n0, i
             cp->actions_out[(size_t)am * N + nn] = o;
           }
         }
-      };
-      epi_rows<RP, BN, CP, NT>(ct, rows, n0, N, f);
+      });
       break;
     }
     default:
@@ -520,27 +481,14 @@ __global__ __launch_bounds__(256) void gemm_tile_rs(GemmArgs a) {
 #pragma unroll
       for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
-        for (int ns = 0; ns < NS; ++ns) mma16(acc[ms][ns], af[ms], bq[ns], bf16_t());
+        for (int ns = 0; ns < NS; ++ns) mma16(acc[ms][ns], bq[ns], af[ms], bf16_t());   // W rows x token rows
     }
     if (more) lstore(buf ^ 1);
     __syncthreads();
     buf ^= 1;
   }
 
-  // Epilogue: the fp32 tile goes through LDS (the K-loop ended with a
-  // barrier), then threads walk it row by row so that consecutive threads
-  // finish consecutive columns.
-  float* ct = reinterpret_cast<float*>(smem);  // [BM][CP]
-  constexpr int CP = BN + 4;
-#pragma unroll
-  for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-    for (int ns = 0; ns < NS; ++ns)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        ct[(wm * 16 * MS + ms * 16 + g4 * 4 + i) * CP + wn * 16 * NS + ns * 16 + r16] = acc[ms][ns][i];
-  __syncthreads();
-  tile_epilogue<BM, BN, CP>(a, ct, m0, n0, split);
+  tile_epilogue<MS, NS>(a, acc, m0 + wm * 16 * MS, n0 + wn * 16 * NS, split);
 }
 
 
@@ -568,7 +516,7 @@ struct Ring {
   static constexpr int NST = ROWS <= 256 ? 4 : (ROWS <= 384 ? 3 : 2);   // stages (LDS <= 144 KB)
   static constexpr int LPT = ROWS * 8 / (64 * NWV);     // load instructions per thread and slice
   static constexpr int SB = ROWS * 8;                   // 16-byte slots per stage
-  // rows of the fp32 output tile per epilogue pass (the tile goes through stage 0)
+  // rows of fp32 partials per epilogue pass through stage 0
   static constexpr int RP = (64 * (BN + 4) * 4 <= SB * 16) ? 64 : (32 * (BN + 4) * 4 <= SB * 16 ? 32 : 16);
 };
 
@@ -611,7 +559,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
     const int chunk = (lane & 7) ^ (row & 7);
     if (row < BM) {
       const int m = min(m0 + row, M - 1);
-      src[i] = reinterpret_cast<const bf16_t*>(a.X) + (size_t)m * a.ldx + k0 + chunk * 8;
+      src[i] = reinterpret_cast<const bf16_t*>(a.X) + act_off<bf16_t>(m, k0 + chunk * 8, a.ldx, a.xt);
     } else {
       const int n = min(n0 + row - BM, N - 1);
       src[i] = reinterpret_cast<const bf16_t*>(a.W) +
@@ -619,12 +567,14 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
     }
   }
   static_assert(BM % (NWV * 8) == 0, "a load instruction holds X rows or W rows");
-  const int wstep = a.wt ? 1024 : 64;   // elements of a W row block per slice: two 16 x 32 tiles, or 64 columns
+  // elements from a slice to the next: 64 columns, or two k-tiles
+  const int wstep = a.wt ? 1024 : 64;
+  const size_t xstep = a.xt ? (size_t)64 * a.xt : 64;
   auto issue = [&](auto j, int sl) {
     v4u* b = stage(j);
 #pragma unroll
     for (int i = 0; i < LPT; ++i)
-      dma16(src[i] + sl * (i * NWV * 8 < BM ? 64 : wstep), b + (i * NWV + wave) * 64);
+      dma16(src[i] + (i * NWV * 8 < BM ? sl * xstep : (size_t)sl * wstep), b + (i * NWV + wave) * 64);
   };
 
   f32x4 acc[MSW][NSW];
@@ -663,8 +613,8 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
         for (int ms = 0; ms < MSW; ++ms)
 #pragma unroll
           for (int ns = 0; ns < NSW; ++ns)
-            acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, af[kq][ms]),
-                                                                  __builtin_bit_cast(bf16x8_t, bq[kq][ns]), acc[ms][ns],
+            acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, bq[kq][ns]),
+                                                                  __builtin_bit_cast(bf16x8_t, af[kq][ms]), acc[ms][ns],
                                                                   0, 0, 0);
     }
   };
@@ -693,12 +643,20 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
           ...);
     }(std::make_integer_sequence<int, NST>{});
   }
-  __builtin_amdgcn_s_waitcnt(vm_wait(0));
-  lds_barrier();
-
-  // epilogue in passes of RP rows through stage 0
-  constexpr int RP = R::RP, CP = BN + 4;
+  if (a.epi != EPI_PARTIAL) {
+    tile_epilogue<MSW, NSW>(a, acc, m0 + wm * 16 * MSW, n0 + wn * 16 * NSW, split);
+    return;
+  }
+  // Split-K partials, fp32: through LDS in passes of RP rows, so that whole
+  // rows of the tile are written at once (a split tile is short, and its
+  // partials are most of what it moves: 400 x 720 from K = 960 in three
+  // splits 7.2 us this way, 8.8 with the accumulators' own 64-byte pieces).
+  constexpr int RP = R::RP, CP = BN + 4, TPR = BN / 4;
   float* ct = reinterpret_cast<float*>(st0);
+  float* out = reinterpret_cast<float*>(a.out) + (size_t)split * M * a.ldo;
+  const bool vec = (a.ldo & 3) == 0;
+  __builtin_amdgcn_s_waitcnt(vm_wait(0));
+  lds_barrier();   // every wave is past its operand reads of stage 0
 #pragma unroll
   for (int p = 0; p < BM / RP; ++p) {
 #pragma unroll
@@ -707,14 +665,17 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
       if (rb / RP == p) {
 #pragma unroll
         for (int ns = 0; ns < NSW; ++ns)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            ct[(rb - p * RP + g4 * 4 + i) * CP + wn * 16 * NSW + ns * 16 + r16] = acc[ms][ns][i];
+          *reinterpret_cast<f32x4*>(ct + (rb - p * RP + r16) * CP + wn * 16 * NSW + ns * 16 + g4 * 4) = acc[ms][ns];
       }
     }
-    lds_barrier();  // LDS only: the epilogue's global stores need not complete here
-    tile_epilogue<RP, BN, CP, 64 * NWV>(a, ct, m0 + p * RP, n0, split);
     lds_barrier();
+#pragma unroll
+    for (int j = 0; j < RP * TPR / (64 * NWV); ++j) {
+      const int idx = tid + 64 * NWV * j, r = idx / TPR, c = idx % TPR * 4;
+      const int m = m0 + p * RP + r, n = n0 + c;
+      if (m < M && n < N) store4n(out + (size_t)m * a.ldo + n, *reinterpret_cast<const f32x4*>(ct + r * CP + c), N - n, vec);
+    }
+    if (p + 1 < BM / RP) lds_barrier();
   }
 }
 
@@ -839,14 +800,14 @@ constexpr TileCand kTiles[kNumTiles] = {{2, 4, 0.34, 4.0}, {4, 4, 0.47, 5.0}, {8
 int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 
 // Time of a skinny launch beyond its fixed latency, in us: the bytes that a
-// compute unit takes in at about 60 GB/s, the rounds of its waves, and what
+// compute unit takes in at about 48 GB/s, the rounds of its waves, and what
 // each split-K partial costs the kernel that sums them.
 double skinny_cost(const SkinnyShape& c, int M, int es) {
   const int rows = M - 16 * c.ms * (c.m_tiles - 1) < 16 * c.ms && c.m_tiles == 1 ? M : 16 * c.ms;
   const double per_cu = (double)cdiv_i(c.units, 256);
   const double bytes = (double)(rows + 16 * c.nsub) * c.kper * es;
   const int rounds = cdiv_i(cdiv_i(c.kper, es == 2 ? 32 : 16), WKS * c.nv);
-  return per_cu * bytes / 60e3 + 0.5 * (rounds - 1) + 0.08 * (c.nsplit - 1) + 0.05 * c.ms * c.nsub;
+  return per_cu * bytes / 48e3 + 0.5 * (rounds - 1) + 0.08 * (c.nsplit - 1) + 0.05 * c.ms * c.nsub;
 }
 
 }  // namespace
@@ -875,7 +836,6 @@ void skinny_shape(int et, int M, int N, int K, int ms, int nsub, int nsplit, Ski
 }
 
 bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, SkinnyShape* sh) {
-  if (M > kSkinnyRows) return false;
   const int es = et == ET_BF16 ? 2 : 4, steps = cdiv_i(K, gemm_chunk_k(et) / VPL);
   double best = 1e30;
   for (int ms = 1; ms <= 4; ms *= 2) {
@@ -891,6 +851,7 @@ bool skinny_plan(int et, int M, int N, int K, int nsub, bool allow_split, Skinny
         if (cost < best) {
           best = cost;
           *sh = c;
+          sh->cost = 2.5 + cost;
         }
       }
       if (nsub == 4) break;
@@ -926,7 +887,6 @@ hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStre
 
 hipError_t launch_gemm_wide(int et, const WideShape& sh, GemmArgs a, hipStream_t s) {
   if (sh.units <= 0) return hipSuccess;
-  if (a.xt) return hipErrorInvalidValue;
   a.n_tiles = sh.n_tiles;
   a.nsplit = 1;
   return et == ET_BF16 ? wide_t<bf16_t>(sh, a, s) : wide_t<float>(sh, a, s);
@@ -955,6 +915,7 @@ bool tile_plan(int et, int M, int N, int K, bool allow_split, int force, TileSha
       const double cost = rounds * unit_us + split_us;
       if (cost < best) {
         best = cost;
+        sh->cost = cost;
         sh->ms = tc.ms; sh->ns = tc.ns; sh->nsplit = nsplit; sh->kper = sps * TBK;
         sh->m_tiles = mt; sh->n_tiles = nt; sh->units = units; sh->grid = cdiv_i(units, 8) * 8;
       }
@@ -977,8 +938,7 @@ hipError_t launch_gemm_tile(const TileShape& sh, GemmArgs a, hipStream_t s) {
   a.m_tiles = sh.m_tiles;
   a.nsplit = sh.nsplit;
   a.kper = sh.kper;
-  // tiled W: whole 64-wide slices (the ring kernel); X is row-major here
-  if (a.xt || a.ot || (a.wt && a.K % 64)) return hipErrorInvalidValue;
+  if ((a.wt || a.xt) && a.K % 64) return hipErrorInvalidValue;   // tiled: the ring kernel's whole slices
   switch (sh.ms * 10 + sh.ns) {
     case 24: return launch_tile_t<2, 4>(sh, a, s);
     case 44: return launch_tile_t<4, 4>(sh, a, s);

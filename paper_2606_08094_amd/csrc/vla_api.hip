@@ -288,9 +288,22 @@ struct DenseLaunch {
 DenseLaunch dense_launch(int et, const GemmArgs& a, int nsub, int variant = 0) {
   DenseLaunch d{};
   const bool split_ok = a.epi == EPI_PARTIAL;
-  if (variant == 0 || variant == 2) d.skinny = skinny_plan(et, a.M, a.N, a.K, nsub, split_ok, &d.sk);
-  if (!d.skinny && (variant == 0 || variant == 3 || variant >= 10))
+  // Above 128 rows the tiled kernel's staging pays, but its latency does not
+  // shrink with the output: a projection without K splits that gives it few
+  // tiles (the head, and narrow projections of a few hundred rows) is still
+  // faster on the skinny one.  160 rows, 960 x 768: 5.3 against 8.3 us; the
+  // 32-wide head of 400 rows 4.5 against 9.1; gate/up 4096 x 768 of 400 rows
+  // 12.3 against 8.4.
+  const bool tiled = a.wt && a.xt;
+  const bool fits = (size_t)a.xt * a.wt * 64 < ((size_t)1 << 31);
+  if ((variant == 0 || variant == 2) && (a.M <= kSkinnyRows || (tiled && et == ET_BF16 && !split_ok)) && fits)
+    d.skinny = skinny_plan(et, a.M, a.N, a.K, nsub, split_ok, &d.sk);
+  if ((!d.skinny || a.M > kSkinnyRows) && (variant == 0 || variant == 3 || variant >= 10))
     d.tile = tile_plan(et, a.M, a.N, a.K, split_ok, variant >= 10 ? variant - 10 : -1, &d.tl);
+  if (d.skinny && d.tile) {
+    d.skinny = d.sk.cost < d.tl.cost;
+    d.tile = !d.skinny;
+  }
   if (!d.skinny && !d.tile) wide_plan(et, a.M, a.N, a.K, nsub, &d.wd);
   return d;
 }
@@ -320,10 +333,11 @@ struct Builder {
     if (a.epi == EPI_PARTIAL) ob = 4.0;
     if (a.epi == EPI_RESID) ob = 8.0;                           // residual read + write
     if (a.epi == EPI_GLU) ob = es * 0.5;                        // one output per gate/up pair
-    const double bytes = (double)a.N * a.K * es + (double)a.M * a.K * xb + (double)a.M * a.N * ob;
+    const int K = a.k_real ? a.k_real : a.K;
+    const double bytes = (double)a.N * K * es + (double)a.M * K * xb + (double)a.M * a.N * ob;
     ops->push_back(Op{[=](hipStream_t s) { return launch_dense(et, dl, a, s); },
-                      op_info(nsub == 2 ? VLA_OP_GEMM_GLU : VLA_OP_GEMM, a.M, a.N, a.K, bytes,
-                              2.0 * a.M * a.N * a.K)});
+                      op_info(nsub == 2 ? VLA_OP_GEMM_GLU : VLA_OP_GEMM, a.M, a.N, K, bytes,
+                              2.0 * a.M * a.N * K)});
   }
 
   void tern(TernArgs a, int nsub) {
@@ -503,10 +517,10 @@ vla_status build_plan(vla_model* m, Plan* p) {
   VLA_TRY(al((void**)&p->a, (size_t)B * n * A * 4));
   VLA_TRY(al((void**)&p->xs, (size_t)B * d * 4));
   VLA_TRY(al((void**)&p->x, (size_t)M * d * 4));
-  // Dense experts: projection inputs in whole slices of 64 columns (zeros past
-  // the width), tiled where the skinny kernel reads them, else row-major
+  // Dense experts: projection inputs tiled, in whole slices of 64 columns
+  // (zeros past the width)
   const bool dense = !m->tern;
-  const int Mp = (M + 15) / 16 * 16, xt = dense && M <= kSkinnyRows ? Mp : 0;
+  const int Mp = (M + 15) / 16 * 16, xt = dense ? Mp : 0;
   const int ldu = dense ? kpad(d) : d, ldx_o = dense ? kpad(dq) : dq, ldh = dense ? kpad(F) : F;
   VLA_TRY(al(&p->u, (size_t)Mp * ldu * (u32 ? 4 : es)));
   int ldqkv = 0;
@@ -710,7 +724,8 @@ vla_status build_plan(vla_model* m, Plan* p) {
 
   // A projection of a dense expert from a padded input buffer
   auto proj = [&](int N, int K, const void* X, const void* W) {
-    GemmArgs g = gemm_base(m, M, N, xt || et == ET_F32 ? K : kpad(K), X, kpad(K), W);
+    GemmArgs g = gemm_base(m, M, N, kpad(K), X, kpad(K), W);
+    g.k_real = K;
     g.wt = kpad(K) / kstep(et);
     g.xt = xt;
     return g;
@@ -729,13 +744,14 @@ vla_status build_plan(vla_model* m, Plan* p) {
       part_need = std::max(part_need, (size_t)dl.splits() * M * d);
       GemmArgs gg = g;
       float** partp = &p->part;
-      const double bytes = (double)g.N * g.K * es + (double)g.M * g.K * es + 4.0 * dl.splits() * g.M * g.N;
+      const int K = g.k_real;
+      const double bytes = (double)g.N * K * es + (double)g.M * K * es + 4.0 * dl.splits() * g.M * g.N;
       bld.ops->push_back(Op{[=](hipStream_t s) {
                               GemmArgs q = gg;
                               q.out = *partp;
                               return launch_dense(et, dl, q, s);
                             },
-                            op_info(VLA_OP_GEMM, g.M, g.N, g.K, bytes, 2.0 * g.M * g.N * g.K)});
+                            op_info(VLA_OP_GEMM, g.M, g.N, K, bytes, 2.0 * g.M * g.N * K)});
       rn.nsplit = dl.splits();
       rn.alpha = alp;
     } else {
@@ -1685,15 +1701,11 @@ vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, 
     g.wt = kt;
     g.X = bufs.x;
     g.ldx = Kp;
-    if (M <= kSkinnyRows) {
-      g.xt = Mp;
-      for (int t = 0; t * ks < K; ++t)
-        HIP_TRY(hipMemcpy2D((char*)bufs.x + (size_t)t * Mp * 64, 64, (const char*)x + (size_t)t * 64, K * es,
-                            std::min(ks, K - t * ks) * es, M, hipMemcpyDeviceToDevice));
-    } else {
-      if (et == ET_BF16) g.K = Kp;
-      HIP_TRY(hipMemcpy2D(bufs.x, Kp * es, x, K * es, K * es, M, hipMemcpyDeviceToDevice));
-    }
+    g.xt = Mp;
+    g.K = Kp;
+    for (int t = 0; t * ks < K; ++t)
+      HIP_TRY(hipMemcpy2D((char*)bufs.x + (size_t)t * Mp * 64, 64, (const char*)x + (size_t)t * 64, K * es,
+                          std::min(ks, K - t * ks) * es, M, hipMemcpyDeviceToDevice));
     HIP_TRY(hipDeviceSynchronize());
     variant = variant == 21 ? 4 : 0;
   }

@@ -36,12 +36,13 @@ enum GemmEpi {
 struct GemmArgs {
   // problem
   int M, N, K;
+  int k_real;              // K without its padding, for the launch's reported work (0 = K)
   const void* X;
   int ldx;
   const void* W;           // [N][K] row-major in the element type, or tiled (wt)
   int wt;                  // k-tiles of a 16-row block when W is tiled (64-byte k-steps, see xtile_off), 0 = row-major
-  int xt;                  // padded rows of X when it is tiled (skinny kernel), 0 = row-major
-  int ot;                  // padded rows of out when the epilogue writes it tiled (skinny kernel), 0 = row-major
+  int xt;                  // padded rows of X when it is tiled, 0 = row-major
+  int ot;                  // padded rows of out when the epilogue writes it tiled, 0 = row-major
   int n_tiles;             // tiles along N (set by the launcher)
   int m_tiles;             // tiles along M (tiled kernel; set by the launcher)
   int nsplit;              // K-splits (set by the launcher; > 1 only with EPI_PARTIAL)
@@ -158,6 +159,7 @@ struct TernArgs {
 struct SkinnyShape {
   int ms, nsub, nv, nsplit, split_log2, kper, n_tiles, m_tiles, units;
   size_t lds;
+  double cost;   // estimated us of a launch
 };
 struct WideShape {
   int ms, nsub, nc, n_tiles, m_tiles, units;
@@ -168,6 +170,7 @@ struct WideShape {
 struct TileShape {
   int ms, ns, nsplit, kper, n_tiles, m_tiles, units, grid;
   size_t lds;
+  double cost;   // estimated us of a launch
 };
 
 // Persistent tensor-parallel denoise loop (bf16, joint attention, batch 1):
@@ -233,7 +236,7 @@ constexpr int PERSIST_MAX_LAYERS = 64;
 
 // Values of one 64-byte k-step, and a reduction length padded to whole slices
 // of every dense kernel (64 values).
-constexpr int kSkinnyRows = 128;   // most token rows of the skinny GEMM
+constexpr int kSkinnyRows = 128;   // row-major operands: most token rows of the skinny GEMM
 inline int kstep(int et) { return et == 1 ? 32 : 16; }
 inline int kpad(int k) { return (k + 63) / 64 * 64; }
 
