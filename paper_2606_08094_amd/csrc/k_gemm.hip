@@ -293,8 +293,9 @@ VLA_DEV void store4n(T* p, f32x4 v, int nv, bool vec) {
 VLA_DEV f32x4 act4(int act, f32x4 v) { return f32x4{act_f(act, v[0]), act_f(act, v[1]), act_f(act, v[2]), act_f(act, v[3])}; }
 
 // acc[ms][ns]: rows mb + 16 ms + r16, columns nb + 16 ns + 4 g4 + i.
+// msn: row subtiles of this wave (MSW, or one less).
 template <int MSW, int NSW>
-VLA_DEV void tile_epilogue(const GemmArgs& a, const f32x4 (&acc)[MSW][NSW], int mb, int nb, int split) {
+VLA_DEV void tile_epilogue(const GemmArgs& a, const f32x4 (&acc)[MSW][NSW], int mb, int nb, int split, int msn = MSW) {
   const int lane = threadIdx.x & 63, r16 = lane & 15, c0 = (lane >> 4) * 4;
   const int M = a.M, N = a.N;
   // f(m, n, nv, v) for every 4-column group that exists
@@ -302,7 +303,7 @@ VLA_DEV void tile_epilogue(const GemmArgs& a, const f32x4 (&acc)[MSW][NSW], int 
 #pragma unroll
     for (int ms = 0; ms < MSW; ++ms) {
       const int m = mb + 16 * ms + r16;
-      if (m >= M) continue;
+      if (ms >= msn || m >= M) continue;
 #pragma unroll
       for (int ns = 0; ns < NSW; ++ns) {
         const int n = nb + 16 * ns + c0;
@@ -317,7 +318,7 @@ VLA_DEV void tile_epilogue(const GemmArgs& a, const f32x4 (&acc)[MSW][NSW], int 
 #pragma unroll
       for (int ms = 0; ms < MSW; ++ms) {
         const int m = mb + 16 * ms + r16;
-        if (m >= M) continue;
+        if (ms >= msn || m >= M) continue;
 #pragma unroll
         for (int j = 0; j < NSW / 2; ++j) {
           const int fc = nb / 2 + 16 * j + c0;
@@ -510,24 +511,30 @@ __global__ __launch_bounds__(256) void gemm_tile_rs(GemmArgs a) {
 // does not change a result.  The 256 x 256 tile (eight waves, 128 x 64 per
 // wave) feeds 128 FLOP per staged byte instead of 85 (256 x 128); its two
 // 64 KB stages fill the LDS, and a slice's MFMAs cover the next slice's load.
-template <int MS, int NS, int NWV = 4>
+//
+// The tile's height is any number MR of 16-row subtiles: the first row of
+// waves takes the larger half, and the waves of one SIMD are one of each row,
+// so an odd MR loads the four SIMDs evenly.  A height that divides the rows
+// well saves the work of padding: 816 rows in four 208-row tiles instead of
+// four of 256, 1600 in eight instead of seven that fill fewer compute units.
+template <int MR, int NS, int NWV>
 struct Ring {
-  static constexpr int BM = 32 * MS, BN = 32 * NS, ROWS = BM + BN;
+  static constexpr int BM = 16 * MR, BN = 32 * NS, ROWS = BM + BN;
   static constexpr int NST = ROWS <= 256 ? 4 : (ROWS <= 384 ? 3 : 2);   // stages (LDS <= 144 KB)
-  static constexpr int LPT = ROWS * 8 / (64 * NWV);     // load instructions per thread and slice
+  static constexpr int NLD = ROWS / 8;                  // load instructions of the workgroup per slice (8 rows each)
+  static constexpr int LPT = (NLD + NWV - 1) / NWV;     // at most, of one wave
+  static constexpr int LASTW = NLD - (LPT - 1) * NWV;   // waves that issue the last one
   static constexpr int SB = ROWS * 8;                   // 16-byte slots per stage
   // rows of fp32 partials per epilogue pass through stage 0
   static constexpr int RP = (64 * (BN + 4) * 4 <= SB * 16) ? 64 : (32 * (BN + 4) * 4 <= SB * 16 ? 32 : 16);
 };
 
-template <int MS, int NS, int NWV = 4>
+template <int MR, int NS, int NWV>
 __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
-  using R = Ring<MS, NS, NWV>;
+  using R = Ring<MR, NS, NWV>;
   constexpr int BM = R::BM, BN = R::BN, NST = R::NST, LPT = R::LPT, SB = R::SB, D = NST - 1;
   constexpr int WN = NWV / 2;                          // waves along N (2 along M)
-  constexpr int MSW = BM / 32, NSW = BN / (16 * WN);   // 16-row / 16-column subtiles of a wave
-  constexpr int KKB = NWV == 8 ? 1 : 2;                // k-halves whose operands are read at once
-  static_assert(LPT * 64 * NWV == R::ROWS * 8, "tile rows");
+  constexpr int MSW = (MR + 1) / 2, NSW = BN / (16 * WN);   // most 16-row / all 16-column subtiles of a wave
   __shared__ v4u st0[SB], st1[SB], st2[NST > 2 ? SB : 1], st3[NST > 3 ? SB : 1];
   auto stage = [&](auto j) -> v4u* {
     constexpr int J = decltype(j)::value;
@@ -539,7 +546,8 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, g4 = lane >> 4;
-  const int wm = wave / WN, wn = wave % WN;
+  const int wm = __builtin_amdgcn_readfirstlane(wave / WN), wn = wave % WN;
+  const int msn = MR % 2 && wm ? MSW - 1 : MSW;   // this wave's row subtiles
   const int M = a.M, N = a.N, K = a.K;
   const int per = gridDim.x >> 3;
   const int u = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
@@ -552,12 +560,18 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
   const int nsl = (min(K, k0 + a.kper) - k0) / 64;
 
   // source of this lane's slot in load instruction i: row (i*NWV + wave)*8 + lane/8
+  // elements from a slice to the next: 64 columns, or two k-tiles
+  const size_t wstep = a.wt ? 1024 : 64, xstep = a.xt ? (size_t)64 * a.xt : 64;
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
   const bf16_t* src[LPT];
+  size_t step[LPT];
 #pragma unroll
   for (int i = 0; i < LPT; ++i) {
     const int row = (i * NWV + wave) * 8 + (lane >> 3);
     const int chunk = (lane & 7) ^ (row & 7);
-    if (row < BM) {
+    const bool isx = (i * NWV + wv) * 8 < BM;   // BM % 8 == 0: an instruction holds X rows or W rows
+    step[i] = isx ? xstep : wstep;
+    if (isx) {
       const int m = min(m0 + row, M - 1);
       src[i] = reinterpret_cast<const bf16_t*>(a.X) + act_off<bf16_t>(m, k0 + chunk * 8, a.ldx, a.xt);
     } else {
@@ -566,15 +580,12 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
                (a.wt ? wtile_off<bf16_t>(n, k0 + chunk * 8, a.wt) : (size_t)n * K + k0 + chunk * 8);
     }
   }
-  static_assert(BM % (NWV * 8) == 0, "a load instruction holds X rows or W rows");
-  // elements from a slice to the next: 64 columns, or two k-tiles
-  const int wstep = a.wt ? 1024 : 64;
-  const size_t xstep = a.xt ? (size_t)64 * a.xt : 64;
+  const bool last_ld = R::LASTW == NWV || wv < R::LASTW;   // this wave issues LPT loads a slice, else LPT - 1
   auto issue = [&](auto j, int sl) {
     v4u* b = stage(j);
 #pragma unroll
     for (int i = 0; i < LPT; ++i)
-      dma16(src[i] + (i * NWV * 8 < BM ? sl * xstep : (size_t)sl * wstep), b + (i * NWV + wave) * 64);
+      if (i + 1 < LPT || last_ld) dma16(src[i] + sl * step[i], b + (i * NWV + wave) * 64);
   };
 
   f32x4 acc[MSW][NSW];
@@ -583,39 +594,34 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
 #pragma unroll
     for (int ns = 0; ns < NSW; ++ns) acc[ms][ns] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // operand rows of this lane and their swizzled slot for logical chunk c.
-  // With four waves every fragment of the slice is read before the first
-  // MFMA, so the LDS latency of the second k-half hides behind the first
-  // half's MFMAs; with eight the other wave of the SIMD hides it, and one
-  // k-half at a time keeps the registers under the two-wave limit.
+  // Operand rows of this lane and their swizzled slot for logical chunk c.
+  // One k-half at a time keeps the registers under the two-wave limit; the
+  // other wave of the SIMD hides the LDS latency.
   auto compute = [&](const v4u* b) {
 #pragma unroll
-    for (int k2 = 0; k2 < 2; k2 += KKB) {
-      v4u af[KKB][MSW], bq[KKB][NSW];
+    for (int kk = 0; kk < 2; ++kk) {
+      v4u af[MSW], bq[NSW];
+      const int c = kk * 4 + g4;
 #pragma unroll
-      for (int kq = 0; kq < KKB; ++kq) {
-        const int c = (k2 + kq) * 4 + g4;
+      for (int ms = 0; ms < MSW; ++ms) {
+        const int row = wm * 16 * MSW + ms * 16 + r16;
+        if (MR % 2 == 0 || ms + 1 < MSW || msn == MSW) af[ms] = b[row * 8 + (c ^ (row & 7))];
+      }
 #pragma unroll
-        for (int ms = 0; ms < MSW; ++ms) {
-          const int row = wm * 16 * MSW + ms * 16 + r16;
-          af[kq][ms] = b[row * 8 + (c ^ (row & 7))];
-        }
-#pragma unroll
-        for (int ns = 0; ns < NSW; ++ns) {
-          const int row = BM + wn * 16 * NSW + ns * 16 + r16;
-          bq[kq][ns] = b[row * 8 + (c ^ (row & 7))];
-        }
+      for (int ns = 0; ns < NSW; ++ns) {
+        const int row = BM + wn * 16 * NSW + ns * 16 + r16;
+        bq[ns] = b[row * 8 + (c ^ (row & 7))];
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kq = 0; kq < KKB; ++kq)
+      for (int ms = 0; ms < MSW; ++ms) {
+        if (MR % 2 && ms + 1 == MSW && msn < MSW) continue;
 #pragma unroll
-        for (int ms = 0; ms < MSW; ++ms)
-#pragma unroll
-          for (int ns = 0; ns < NSW; ++ns)
-            acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, bq[kq][ns]),
-                                                                  __builtin_bit_cast(bf16x8_t, af[kq][ms]), acc[ms][ns],
-                                                                  0, 0, 0);
+        for (int ns = 0; ns < NSW; ++ns)
+          acc[ms][ns] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, bq[ns]),
+                                                                __builtin_bit_cast(bf16x8_t, af[ms]), acc[ms][ns],
+                                                                0, 0, 0);
+      }
     }
   };
 
@@ -631,10 +637,12 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
             const int it = it0 + J;
             if (it >= nsl) return;
             // slice `it` has landed once at most the D-1 later slices are pending
-            if (it + D - 1 < nsl)
-              __builtin_amdgcn_s_waitcnt(vm_wait((D - 1) * LPT));
-            else
+            if (it + D - 1 < nsl) {
+              if (last_ld) __builtin_amdgcn_s_waitcnt(vm_wait((D - 1) * LPT));
+              else __builtin_amdgcn_s_waitcnt(vm_wait((D - 1) * (LPT - 1)));
+            } else {
               __builtin_amdgcn_s_waitcnt(vm_wait(0));
+            }
             lds_barrier();
             // the stage of slice it-1 is free: refill it with slice it+D
             if (it + D < nsl) issue(std::integral_constant<int, (J + D) % NST>{}, it + D);
@@ -644,7 +652,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
     }(std::make_integer_sequence<int, NST>{});
   }
   if (a.epi != EPI_PARTIAL) {
-    tile_epilogue<MSW, NSW>(a, acc, m0 + wm * 16 * MSW, n0 + wn * 16 * NSW, split);
+    tile_epilogue<MSW, NSW>(a, acc, m0 + wm * 16 * MSW, n0 + wn * 16 * NSW, split, msn);
     return;
   }
   // Split-K partials, fp32: through LDS in passes of RP rows, so that whole
@@ -658,11 +666,11 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
   __builtin_amdgcn_s_waitcnt(vm_wait(0));
   lds_barrier();   // every wave is past its operand reads of stage 0
 #pragma unroll
-  for (int p = 0; p < BM / RP; ++p) {
+  for (int p = 0; p < (BM + RP - 1) / RP; ++p) {
 #pragma unroll
     for (int ms = 0; ms < MSW; ++ms) {
       const int rb = wm * 16 * MSW + ms * 16;  // first row of subtile ms
-      if (rb / RP == p) {
+      if (rb / RP == p && ms < msn) {
 #pragma unroll
         for (int ns = 0; ns < NSW; ++ns)
           *reinterpret_cast<f32x4*>(ct + (rb - p * RP + r16) * CP + wn * 16 * NSW + ns * 16 + g4 * 4) = acc[ms][ns];
@@ -673,9 +681,9 @@ __global__ __launch_bounds__(64 * NWV) void gemm_tile(GemmArgs a) {
     for (int j = 0; j < RP * TPR / (64 * NWV); ++j) {
       const int idx = tid + 64 * NWV * j, r = idx / TPR, c = idx % TPR * 4;
       const int m = m0 + p * RP + r, n = n0 + c;
-      if (m < M && n < N) store4n(out + (size_t)m * a.ldo + n, *reinterpret_cast<const f32x4*>(ct + r * CP + c), N - n, vec);
+      if (p * RP + r < BM && m < M && n < N) store4n(out + (size_t)m * a.ldo + n, *reinterpret_cast<const f32x4*>(ct + r * CP + c), N - n, vec);
     }
-    if (p + 1 < BM / RP) lds_barrier();
+    if ((p + 1) * RP < BM) lds_barrier();
   }
 }
 
@@ -767,35 +775,37 @@ hipError_t wide_t(const WideShape& sh, const GemmArgs& a, hipStream_t s) {
 // K % 64 == 0: the direct-to-LDS ring on eight waves (two per SIMD, so one
 // wave's LDS and load waits hide behind the other's MFMAs: 12-17% faster than
 // four waves on every tile); else the register-staged kernel on four.
-template <int MS, int NS>
+template <int MR, int NS>
 hipError_t launch_tile_t(const TileShape& sh, const GemmArgs& a, hipStream_t s) {
   if (a.K % 64 == 0) {
-    hipLaunchKernelGGL((gemm_tile<MS, NS, 8>), dim3(sh.grid), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((gemm_tile<MR, NS, 8>), dim3(sh.grid), dim3(512), 0, s, a);
     return hipGetLastError();
   }
-  if constexpr (MS * NS > 32) {   // 256 x 256: the ring only
+  if constexpr (MR % 4 || MR * NS > 64) {   // the ring only
     return hipErrorInvalidValue;
   } else {
     static bool attr = false;
     if (!attr) {
-      hipError_t e = set_lds_attr(&gemm_tile_rs<MS, NS>);
+      hipError_t e = set_lds_attr(&gemm_tile_rs<MR / 2, NS>);
       if (e != hipSuccess) return e;
       attr = true;
     }
-    const size_t lds = tile_lds_bytes<MS, NS>();
-    hipLaunchKernelGGL((gemm_tile_rs<MS, NS>), dim3(sh.grid), dim3(256), lds, s, a);
+    const size_t lds = tile_lds_bytes<MR / 2, NS>();
+    hipLaunchKernelGGL((gemm_tile_rs<MR / 2, NS>), dim3(sh.grid), dim3(256), lds, s, a);
     return hipGetLastError();
   }
 }
 
-// The tiles gemm_tile is instantiated for, as (MS, NS), with the measured
-// time of one 64-wide K-slice of a workgroup on eight waves (microseconds, one
-// workgroup per compute unit: bound by the operand bytes a compute unit takes
-// in from L2) and the fixed cost of a workgroup (pipeline fill, epilogue).
-struct TileCand { int ms, ns; double slice_us, fixed_us; };
-constexpr int kNumTiles = 5;
-constexpr TileCand kTiles[kNumTiles] = {{2, 4, 0.34, 4.0}, {4, 4, 0.47, 5.0}, {8, 4, 0.80, 6.0}, {4, 8, 0.80, 6.0},
-                                        {8, 8, 1.6, 8.0}};   // 256 x 256: K % 64 == 0 only
+// The tiles gemm_tile is instantiated for, as (16-row subtiles, 32-column
+// pairs), with the measured time of one 64-wide K-slice of a workgroup on eight
+// waves (microseconds, one workgroup per compute unit: bound by the operand
+// bytes a compute unit takes in from L2) and the fixed cost of a workgroup
+// (pipeline fill, epilogue).
+struct TileCand { int mr, ns; double slice_us, fixed_us; };
+constexpr int kNumTiles = 8;
+constexpr TileCand kTiles[kNumTiles] = {{4, 4, 0.34, 4.0}, {8, 4, 0.47, 5.0}, {16, 4, 0.80, 6.0}, {8, 8, 0.80, 6.0},
+                                        {16, 8, 1.6, 8.0},   // from here K % 64 == 0 only
+                                        {10, 4, 0.55, 5.3}, {13, 4, 0.67, 5.6}, {13, 8, 1.32, 7.2}};
 
 int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 
@@ -899,8 +909,8 @@ bool tile_plan(int et, int M, int N, int K, bool allow_split, int force, TileSha
   for (int c = 0; c < kNumTiles; ++c) {
     if (force >= 0 && c != force) continue;
     const TileCand& tc = kTiles[c];
-    if (tc.ms * tc.ns > 32 && K % 64) continue;   // the eight-wave tile runs on the direct-to-LDS ring only
-    const int BM = 32 * tc.ms, BN = 32 * tc.ns;
+    if (c >= 4 && K % 64) continue;   // the direct-to-LDS ring only
+    const int BM = 16 * tc.mr, BN = 32 * tc.ns;
     const int mt = cdiv_i(M, BM), nt = cdiv_i(N, BN);
     const int max_split = (allow_split && force < 0) ? std::min(8, slices) : 1;
     for (int ns = 1; ns <= max_split; ++ns) {
@@ -916,19 +926,12 @@ bool tile_plan(int et, int M, int N, int K, bool allow_split, int force, TileSha
       if (cost < best) {
         best = cost;
         sh->cost = cost;
-        sh->ms = tc.ms; sh->ns = tc.ns; sh->nsplit = nsplit; sh->kper = sps * TBK;
+        sh->mr = tc.mr; sh->ns = tc.ns; sh->nsplit = nsplit; sh->kper = sps * TBK;
         sh->m_tiles = mt; sh->n_tiles = nt; sh->units = units; sh->grid = cdiv_i(units, 8) * 8;
       }
     }
   }
   if (best >= 1e30) return false;
-  switch (sh->ms * 10 + sh->ns) {
-    case 24: sh->lds = tile_lds_bytes<2, 4>(); break;
-    case 44: sh->lds = tile_lds_bytes<4, 4>(); break;
-    case 84: sh->lds = tile_lds_bytes<8, 4>(); break;
-    case 48: sh->lds = tile_lds_bytes<4, 8>(); break;
-    default: sh->lds = 0; break;   // 256 x 256: static LDS only
-  }
   return true;
 }
 
@@ -939,12 +942,15 @@ hipError_t launch_gemm_tile(const TileShape& sh, GemmArgs a, hipStream_t s) {
   a.nsplit = sh.nsplit;
   a.kper = sh.kper;
   if ((a.wt || a.xt) && a.K % 64) return hipErrorInvalidValue;   // tiled: the ring kernel's whole slices
-  switch (sh.ms * 10 + sh.ns) {
-    case 24: return launch_tile_t<2, 4>(sh, a, s);
+  switch (sh.mr * 10 + sh.ns) {
     case 44: return launch_tile_t<4, 4>(sh, a, s);
     case 84: return launch_tile_t<8, 4>(sh, a, s);
-    case 48: return launch_tile_t<4, 8>(sh, a, s);
+    case 164: return launch_tile_t<16, 4>(sh, a, s);
     case 88: return launch_tile_t<8, 8>(sh, a, s);
+    case 168: return launch_tile_t<16, 8>(sh, a, s);
+    case 104: return launch_tile_t<10, 4>(sh, a, s);
+    case 134: return launch_tile_t<13, 4>(sh, a, s);
+    case 138: return launch_tile_t<13, 8>(sh, a, s);
   }
   return hipErrorInvalidValue;
 }

@@ -165,11 +165,10 @@ struct WideShape {
   int ms, nsub, nc, n_tiles, m_tiles, units;
   size_t lds;
 };
-// Tiled kernel: a (32*ms) x (32*ns) output tile per workgroup, K split in
+// Tiled kernel: a (16*mr) x (32*ns) output tile per workgroup, K split in
 // nsplit ranges of kper.  grid = units rounded up to a multiple of 8.
 struct TileShape {
-  int ms, ns, nsplit, kper, n_tiles, m_tiles, units, grid;
-  size_t lds;
+  int mr, ns, nsplit, kper, n_tiles, m_tiles, units, grid;
   double cost;   // estimated us of a launch
 };
 

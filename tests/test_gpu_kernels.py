@@ -78,6 +78,22 @@ def test_gemm_parity(torch, elem, M, N, K):
         assert np.all(err <= bound), f"variant={variant} max err {err.max()} worst ratio {(err / bound).max()}"
 
 
+@pytest.mark.parametrize("variant", [15, 16, 17])
+@pytest.mark.parametrize("M,N,K", [(129, 128, 64), (160, 130, 128), (161, 256, 192), (208, 257, 320), (209, 64, 1024),
+                                   (416, 384, 256), (417, 100, 64), (816, 512, 2048)])
+def test_gemm_tile_heights(torch, M, N, K, variant):
+    """Tiles of 160 and 208 rows (an odd number of 16-row subtiles: one row of waves holds one more): last tiles
+    of 1, 16 and all rows, ragged columns, one K slice to many."""
+    seed = 1000 * M + N + K
+    x = wl.random_matrix((M, K), seed, 1.0, bf16=True)
+    w = wl.random_matrix((N, K), seed + 1, 0.05, bf16=True)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    _vla().test_gemm(1, _dev(torch, x, True), _dev(torch, w, True), M, N, K, y, variant=variant)
+    err = np.abs(y.cpu().numpy().astype(np.float64) - O.linear(x, w))
+    bound = _fp32_bound(x.astype(np.float64), w.astype(np.float64))
+    assert np.all(err <= bound), f"max err {err.max()} worst ratio {(err / bound).max()}"
+
+
 @pytest.mark.parametrize("elem", [1, 0])
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm_tiled_operands(torch, elem, M, N, K):
