@@ -14,7 +14,7 @@
 //   MFMA, so a workgroup pays one memory latency per round instead of one per
 //   staging step.  The eight partial tiles are summed in wave order through
 //   LDS and waves 0..MS-1 run the epilogue of one 16-row subtile each.
-//   What bounds it is the bytes a compute unit takes in (about 60 GB/s) and
+//   What bounds it is the bytes a compute unit takes in (about 48 GB/s) and
 //   the fixed latency of a launch, so the tile is the one that spreads the
 //   least bytes over 256 compute units (skinny_cost).  In a chain of cold
 //   weights, against tiles that always hold every token row with branchy loads
@@ -27,14 +27,14 @@
 //   inside the workgroup.
 //
 // gemm_tile -- bf16 with M > 128 (batched requests, the prefix K/V build),
-//   where the work is MFMA-bound.  Four waves (2 x 2) own a BM x BN output tile
-//   (BM = 32*MS, BN = 32*NS); X and W are both staged through LDS in K-slices
-//   of 64, double-buffered: the global loads of slice s+1 are in flight while
-//   the MFMAs of slice s run, and one barrier per slice separates the two
-//   buffers.  LDS rows are padded by 16 bytes so that the rows of one MFMA
-//   operand load fall in distinct banks.  Tiles along M are numbered fastest
-//   and blocks are renumbered so that consecutive tiles (which share one W
-//   slice) run on the same XCD and its L2.
+//   where LDS bandwidth and the MFMAs bound the work.  Eight waves (2 x 4) own
+//   a (16*MR) x (32*NS) output tile; slices of 64 k-values of X and W stream
+//   into a ring of LDS stages by direct-to-LDS loads, several slices ahead of
+//   the MFMAs, and the epilogue stores from the accumulators.  A K that is not
+//   a multiple of 64 takes gemm_tile_rs instead: four waves (2 x 2), the next
+//   slice's loads held in registers during the MFMAs, padded LDS rows.  Tiles
+//   along M are numbered fastest and blocks are renumbered so that consecutive
+//   tiles (which share one W slice) run on the same XCD and its L2.
 //
 // Operand layout: in a chunk, lane l of a wave reads 16-byte vector v of row
 // (l % 16) at k-offset v*4*E + (l/16)*E, for W and X alike, so the MFMA's k

@@ -249,8 +249,8 @@ void wide_plan(int et, int M, int N, int K, int nsub, WideShape* sh);
 hipError_t launch_gemm_skinny(int et, const SkinnyShape& sh, GemmArgs a, hipStream_t s);
 hipError_t launch_gemm_wide(int et, const WideShape& sh, GemmArgs a, hipStream_t s);
 // Tiled bf16 kernel for M > 128.  force < 0: the cost model picks the tile and
-// the K-split (split only if allow_split); force = 0..3 fixes the tile
-// (64x128, 128x128, 256x128, 128x256) with no split.  False if not applicable.
+// the K-split (split only if allow_split); force = 0..7 fixes the tile (the
+// planner's list, in its order) with no split.  False if not applicable.
 bool tile_plan(int et, int M, int N, int K, bool allow_split, int force, TileShape* sh);
 hipError_t launch_gemm_tile(const TileShape& sh, GemmArgs a, hipStream_t s);
 

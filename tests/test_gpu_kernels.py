@@ -78,7 +78,7 @@ def test_gemm_parity(torch, elem, M, N, K):
         assert np.all(err <= bound), f"variant={variant} max err {err.max()} worst ratio {(err / bound).max()}"
 
 
-@pytest.mark.parametrize("variant", [15, 16, 17])
+@pytest.mark.parametrize("variant", [22, 23, 24])
 @pytest.mark.parametrize("M,N,K", [(129, 128, 64), (160, 130, 128), (161, 256, 192), (208, 257, 320), (209, 64, 1024),
                                    (416, 384, 256), (417, 100, 64), (816, 512, 2048)])
 def test_gemm_tile_heights(torch, M, N, K, variant):
