@@ -972,8 +972,10 @@ vla_status run_ops_profiled(Plan* p, hipStream_t s, int reps) {
 }  // namespace
 
 vla_model::~vla_model() {
-  if (persist_counted) persist_gate().add(-1);
+  // a persistent plan waits here for its launch in flight; until then the
+  // other models' launches wait for it too
   plans.clear();
+  if (persist_counted) persist_gate().add(-1);
   prefix_ws.clear();
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
   for (void* p : allocs) (void)hipFree(p);
