@@ -161,7 +161,10 @@ vla_status vla_prefix_kv_build_noalloc(vla_model* model, const void* prefix_hidd
  * failed call has completed.  Each launch starts with a cleared record, so
  * one failure does not affect later calls.  The persistent kernel takes every
  * compute unit at once; where several models of a process use it, its launches
- * on one device run one after another, whatever their streams.
+ * on one device run one after another, whatever their streams.  Calls captured
+ * into a graph are outside that order: the caller sees to it that a replay does
+ * not run beside another model's vla_denoise or replay on the device (one
+ * stream for all of them, or events); side by side they can time out as above.
  */
 vla_status vla_denoise(vla_model* model, const void* kv_cache, size_t kv_cache_bytes, int32_t batch,
                        int32_t prefix_len, const float* noise, const float* state,

@@ -439,29 +439,30 @@ int mlp_act(int mlp) {
 // has a persistent plan, every launch on a device waits (on the device, by an
 // event) for the previous one there.  A model's first persistent plan is
 // counted before the device synchronisation that ends its build, so launches
-// made earlier, without an event, have completed by then.
+// made earlier, without an event, have completed by then.  A launch captured
+// by the caller cannot wait for an event recorded outside its capture and goes
+// in as it is: the order of replays is the caller's (vla.h says so).
 struct PersistGate {
-  static constexpr int kDevices = 64;
   std::mutex mx;
   int models = 0;
-  hipEvent_t last[kDevices] = {};
+  std::map<int, hipEvent_t> last;   // per device: recorded after its latest launch
   hipError_t launch(const PersistArgs& a, hipStream_t s) {
     std::lock_guard<std::mutex> lk(mx);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (models < 2) return launch_persist(a, s);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;   // the null stream is never captured
     int dev = 0;
     hipError_t e;
-    if (models < 2) return launch_persist(a, s);
-    const bool known = hipStreamIsCapturing(s, &cap) == hipSuccess && hipGetDevice(&dev) == hipSuccess;
-    if (!known) (void)hipGetLastError();
-    // a captured launch cannot wait for an event recorded outside its capture
-    if (!known || cap != hipStreamCaptureStatusNone || dev >= kDevices) return launch_persist(a, s);
-    if (!last[dev]) {
-      if ((e = hipEventCreateWithFlags(&last[dev], hipEventDisableTiming)) != hipSuccess) return e;
-    } else if ((e = hipStreamWaitEvent(s, last[dev], 0)) != hipSuccess) {
+    if (s != nullptr && (e = hipStreamIsCapturing(s, &cap)) != hipSuccess) return e;
+    if (cap != hipStreamCaptureStatusNone) return launch_persist(a, s);
+    if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+    hipEvent_t& ev = last[dev];
+    if (!ev) {
+      if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
+    } else if ((e = hipStreamWaitEvent(s, ev, 0)) != hipSuccess) {
       return e;
     }
     if ((e = launch_persist(a, s)) != hipSuccess) return e;
-    return hipEventRecord(last[dev], s);
+    return hipEventRecord(ev, s);
   }
   void add(int n) {
     std::lock_guard<std::mutex> lk(mx);

@@ -12,6 +12,7 @@ static char log_buf[1 << 20];
 static size_t log_len;
 static int n_events;
 static int capture_status, capture_error;   /* what hipStreamIsCapturing reports */
+static int device;
 static sync_fn on_sync;                     /* called once, inside the next hipDeviceSynchronize */
 
 static void note(const char* what, void* stream, void* event) {
@@ -22,6 +23,7 @@ static void note(const char* what, void* stream, void* event) {
 const char* stub_log(void) { return log_buf; }
 void stub_clear(void) { log_len = 0; log_buf[0] = 0; }
 void stub_capture(int status, int error) { capture_status = status; capture_error = error; }
+void stub_device(int d) { device = d; }
 void stub_on_sync(sync_fn f) { on_sync = f; }
 
 int hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? 0 : 2; }
@@ -41,7 +43,7 @@ int hipMemcpy2D(void* d, size_t dp, const void* s, size_t sp, size_t w, size_t h
 int hipMemset(void* p, int v, size_t n) { memset(p, v, n); return 0; }
 int hipMemsetAsync(void* p, int v, size_t n, void* st) { (void)st; return hipMemset(p, v, n); }
 int hipGetLastError(void) { return 0; }
-int hipGetDevice(int* d) { *d = 0; return 0; }
+int hipGetDevice(int* d) { *d = device; return 0; }
 int hipDeviceGetAttribute(int* v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void* f, int b, size_t l) {

@@ -68,6 +68,38 @@ assert [e[0] for e in got] == ["sync", "wait", "persist", "record"], got
 denoise(a, 0x10)   # alone again
 assert [e[0] for e in events()] == ["persist"]
 ''',
+    # a captured call cannot wait for an event of work outside its capture: it goes in without events, in the
+    # caller's order; a stream whose state cannot be told gets no launch at all
+    "capture": r'''
+a, b = model(), model()
+denoise(a, 0x10); denoise(b, 0x20); events()
+stub.stub_capture(1, 0)
+denoise(a, 0x10)
+assert [e[:2] for e in events()] == [("persist", 0x10)]
+stub.stub_capture(0, 0)
+denoise(b, 0x20)
+assert [e[0] for e in events()] == ["wait", "persist", "record"]
+stub.stub_capture(0, 906)
+try:
+    denoise(a, 0x10)
+except vla.VlaError as e:
+    assert vla.STATUS[e.status] == "VLA_E_DEVICE", e
+else:
+    raise AssertionError("accepted")
+assert events() == []
+denoise(a, 0)      # the null stream is never captured
+assert [e[0] for e in events()] == ["wait", "persist", "record"]
+''',
+    # each device has its own order, whatever its number
+    "devices": r'''
+a, b = model(), model()
+denoise(a, 0x10); denoise(b, 0x20)
+for dev in (3, 70):
+    stub.stub_device(dev)
+    denoise(a, 0x10); events()
+    denoise(b, 0x20)
+    assert [e[0] for e in events()] == ["wait", "persist", "record"], dev
+''',
 }
 
 
