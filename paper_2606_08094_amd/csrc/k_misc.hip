@@ -211,14 +211,17 @@ __global__ __launch_bounds__(256) void row_norm_kernel(RowNormArgs a) {
   if ((t & 63) == 0) red[t >> 6] = ss;
   lds_barrier();   // LDS only: the stores of x complete behind the rest
   const float rows = red[0] + red[1] + red[2] + red[3];
+  const float ms = rows * inv_d + a.eps;
   float rstd;
-  if (a.exact) {
+  if (a.exact || !(ms >= 0x1p-126f && ms < INFINITY)) {
     // W2A8 models: correctly rounded steps, so that the int8 codes of u, and
-    // all that follows from them, do not hang on the hardware's estimate
+    // all that follows from them, do not hang on the hardware's estimate.  And
+    // every model past the normal range, where the Newton step would make an
+    // infinite, denormal or zero mean square NaN: infinity gives 0 (u = beta),
+    // a denormal its root.
     rstd = 1.0f / sqrtf(rows / (float)d + a.eps);
   } else {
     // the hardware estimate (1 ulp) and one Newton step
-    const float ms = rows * inv_d + a.eps;
     rstd = __builtin_amdgcn_rsqf(ms);
     rstd = rstd + 0.5f * rstd * (1.0f - ms * rstd * rstd);
   }

@@ -251,6 +251,34 @@ def test_adarms_parity(torch, elem, u_f32, M, d, nsplit):
     assert np.all(np.abs(u_got - u_ref) <= rel * np.abs(u_ref) + 1e-5), np.abs(u_got - u_ref).max()
 
 
+@pytest.mark.parametrize("elem,u_f32", [(0, 0), (1, 0), (1, 1)])
+@pytest.mark.parametrize("d", [256, 1600, 4096])
+def test_adarms_ends_of_range(torch, elem, u_f32, d):
+    """Rows whose mean square leaves the normal fp32 range: past its end the reciprocal root is 0 and u = beta; a
+    row of zeros under a denormal eps gives beta; a denormal mean square (1.1e-38) gives its own root; an infinite
+    value makes its row NaN (0 * inf) and leaves the others alone."""
+    rng = np.random.default_rng(d)
+    gamma = (0.3 * rng.standard_normal(d)).astype(np.float32)
+    beta = (0.3 * rng.standard_normal(d)).astype(np.float32)
+    eps = 1e-39
+    x = np.zeros((5, d), np.float32)
+    x[0] = rng.choice([-1e20, 2e20], d)
+    x[2] = rng.choice([-1e-19, 1e-19], d)
+    x[3] = rng.standard_normal(d)
+    x[4] = x[3]
+    x[3, d // 2] = np.inf
+    u = torch.empty((5, d), dtype=torch.float32 if u_f32 or elem == 0 else torch.bfloat16, device="cuda")
+    dev = [torch.from_numpy(v).cuda() for v in (x, gamma, beta)]
+    _vla().test_adarms(elem, dev[0], None, 0, None, dev[1], dev[2], 5, d, eps, u, bool(u_f32))
+    got = u.float().cpu().numpy().astype(np.float64)
+    want = O.ada_rms(x[[1, 1, 2, 4, 4]].astype(np.float64), gamma, beta, eps)   # rows 0 and 1: beta
+    rows = [0, 1, 2, 4]
+    # bf16: half a unit of its 8 bits; fp32: 1e-5, and squares near 1e-38 hold 23 bits less 1 to 2
+    rel = 2.0 ** -8 if (elem == 1 and not u_f32) else 1e-5
+    assert np.all(np.abs(got - want)[rows] <= rel * np.abs(want)[rows] + 1e-5), np.abs(got - want)[rows].max(axis=1)
+    assert np.isnan(got[3, d // 2])
+
+
 @pytest.mark.parametrize("name", ["tiny_f32", "pi0_bf16", "smolvla_bf16"])
 def test_time_cond_parity(torch, name):
     """Time-conditioning precompute (sinusoid, time MLP, every layer's W_mod and
