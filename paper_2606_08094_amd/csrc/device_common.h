@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "tile_addr.h"
 #include "vla_internal.h"
 
 typedef uint16_t bf16_t;  // bf16 storage
@@ -105,10 +106,9 @@ template <typename T> VLA_DEV size_t act_off(int row, int k, int ld, int rows_pa
   return rows_pad ? xtile_off<T>(row, k, rows_pad) : (size_t)row * ld + k;
 }
 
-// Buffer loads: a resource over [base, base + bytes); loads past its end (kOob
-// always is, for buffers below 2 GiB) read zero without a branch.
+// Buffer loads: a resource over [base, base + bytes); loads whose lane offset
+// is past its end (kOob always is) read zero without a branch.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
-constexpr unsigned kOob = 0x7ffffff0u;
 VLA_DEV rsrc_t make_rsrc(const void* base, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }

@@ -128,22 +128,25 @@ __global__ __launch_bounds__(64 * WKS) void gemm_skinny(GemmArgs a) {
     uint4 wreg[NSUB][NV], xreg[MS][NV];
     const int kl = kr + g4 * E;
     if constexpr (TL) {
-      // a step past the range (the last wave's) loads zeros from past the
-      // buffer's end, and no row of X past the padded ones is read
+      // a step past the range (the last wave's) or a subtile past N loads
+      // zeros from past the buffer's end, and no row of X past the padded ones
+      // is read
       const unsigned lo = (unsigned)(r16 * 64 + g4 * 16), kb = (unsigned)(kr / KSTEP), ke = (unsigned)((k1 + KSTEP - 1) / KSTEP);
+      const int subs = min((a.N - nb + 15) >> 4, NSUB);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const unsigned lv = kb + v < ke ? lo : kOob;
+      for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int s = 0; s < NSUB; ++s) wreg[s][v] = buf_ld16(W, lv, ((unsigned)(s * a.wt) + kb + v) * 1024u);
-      }
+        for (int s = 0; s < NSUB; ++s) {
+          const TileLoad at = skinny_w_at(lo, s, subs, kb + v, ke, a.wt);
+          wreg[s][v] = buf_ld16(W, at.lane, at.uni);
+        }
 #pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const bool ok = kb + v < ke;
+      for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int ms = 0; ms < MS; ++ms)
-          xreg[ms][v] = buf_ld16(X, ok && m0 + ms * 16 < a.xt ? lo : kOob, ((kb + v) * (unsigned)a.xt + (unsigned)(m0 + ms * 16)) * 64u);
-      }
+        for (int ms = 0; ms < MS; ++ms) {
+          const TileLoad at = skinny_x_at(lo, m0 + ms * 16, a.xt, kb + v, ke);
+          xreg[ms][v] = buf_ld16(X, at.lane, at.uni);
+        }
     } else {
     unsigned wo[NSUB], xo[MS];
 #pragma unroll
