@@ -196,7 +196,8 @@ struct WTile {
 };
 
 // W: tiled [rows / 16][K / 32][16][32] bf16 (rsrc over the matrix); wrow[s] < 0: tile s absent.
-template <int NS>
+// TAIL: K may end inside a chunk, whose k-steps past it are zero like absent chunks.
+template <int NS, bool TAIL>
 VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int K, const int (&wrow)[NS]) {
   // the wave index in a scalar register: the row-block offsets derived from it
   // are scalar, so each load is one instruction (no loop over lane values)
@@ -209,9 +210,14 @@ VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int K, const int (&wrow)[NS]) {
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const bool on = kc < K && wrow[s] >= 0;
-      const unsigned sb = on ? ((unsigned)(wrow[s] >> 4) * (unsigned)(K >> 5) + (unsigned)(kc >> 5)) * 1024u : 0u;
 #pragma unroll
-      for (int v = 0; v < VPL; ++v) t.w[j][s][v] = on ? bld16(W, vb + 1024u * v, sb, 0) : make_uint4(0, 0, 0, 0);
+      for (int v = 0; v < VPL; ++v) {
+        const TileLoad at = team_w_at<TAIL>(vb, on ? wrow[s] : 0, on ? kc : 0, v, K);
+        // a branch of the wave, not a select of its lanes, which costs the
+        // kernel registers
+        if (on && (!TAIL || kc + 32 * v < K)) t.w[j][s][v] = bld16(W, at.lane, at.uni, 0);
+        else t.w[j][s][v] = make_uint4(0, 0, 0, 0);
+      }
     }
   }
 }
@@ -274,7 +280,9 @@ VLA_DEV void vm_wait_mem() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "me
 // wave's groups come in with one load (lane l: group l / 8, row 48 + (l / 4) % 2,
 // k part l % 4) instead of one mostly out-of-range load per group.  A load
 // costs the address unit the same whether its lanes are in range or not.
-template <int NS, int NCH, bool FOLD>
+// TAIL: K <= 512 NCH in whole k-steps of 32; else K = 512 NCH, so every chunk
+// of every wave is whole.
+template <int NS, int NCH, bool FOLD, bool TAIL>
 VLA_DEV void tile_mma(f32x4 (&acc)[4][NS], const WTile<NS>& t, const void* xbase, unsigned xbytes, int K, int M,
                       unsigned char* stage) {
   static_assert(NCH >= 1 && NCH <= CPW && (!FOLD || NCH * VPL <= 8), "tile_mma shape");
@@ -308,8 +316,8 @@ VLA_DEV void tile_mma(f32x4 (&acc)[4][NS], const WTile<NS>& t, const void* xbase
     for (int v = 0; v < VPL; ++v)
 #pragma unroll
       for (int ms = 0; ms < LPG; ++ms) {
-        const unsigned so = kc < K ? (unsigned)(((kc >> 5) + v) * M * 64 + ms * 16 * 64) : 0x7ffffff0u;
-        dma_x16(rs, vo[ms], so, stage, (unsigned)(wave * XSTAGE + ((j * VPL + v) * 4 + ms) * 1024));
+        const TileLoad at = team_x_at<TAIL>(vo[ms], ms, kc, v, K, M);
+        dma_x16(rs, at.lane, at.uni, stage, (unsigned)(wave * XSTAGE + ((j * VPL + v) * 4 + ms) * 1024));
       }
   }
 #pragma unroll
@@ -798,7 +806,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   {
     int wr[2], oc[2];
     qkv_rows(wr, oc);
-    prefetch_w<2>(wq, mkr(lt[0].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
+    prefetch_w<2, false>(wq, mkr(lt[0].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
   }
   embed();
   norm_store(gam(0, 0, 0), gam(0, 0, 0) + d);
@@ -815,7 +823,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         int wr[2], oc[2];
         qkv_rows(wr, oc);
         f32x4 acc[4][2];
-        tile_mma<2, DPT / 2, FOLD>(acc, wq, ubase, (unsigned)(n * d * 2), d, n, smem);
+        tile_mma<2, DPT / 2, FOLD, false>(acc, wq, ubase, (unsigned)(n * d * 2), d, n, smem);
         __syncthreads();
         tile_reduce<2>(acc, red);
         if constexpr (VAR) {
@@ -1137,7 +1145,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         gu_rows(wr);
-        prefetch_w<2>(wg, mkr(ly.wgu, (size_t)(a.glu ? 2 : 1) * a.F * d * 2), d, wr);
+        prefetch_w<2, false>(wg, mkr(ly.wgu, (size_t)(a.glu ? 2 : 1) * a.F * d * 2), d, wr);
       }
       if (!wait_flags<true>(sy, team, &flag, pk3)) return bail();
       mark();
@@ -1153,7 +1161,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       // ---- G: u -> h of the team's MLP columns ------------------------------------
       {
         f32x4 acc[4][2];
-        tile_mma<2, DPT / 2, FOLD>(acc, wg, ubase, (unsigned)(n * d * 2), d, n, smem);
+        tile_mma<2, DPT / 2, FOLD, false>(acc, wg, ubase, (unsigned)(n * d * 2), d, n, smem);
         __syncthreads();
         tile_reduce<2>(acc, red);
         if (rank < npairs) {
@@ -1194,7 +1202,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         dn_rows(wr);
-        prefetch_w<2>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
+        prefetch_w<2, true>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
       }
       if (!wait_flags<false>(sy, team, &flag, pk4)) return bail();
       mark();
@@ -1204,7 +1212,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         int wr[2];
         dn_rows(wr);
         f32x4 acc[4][2];
-        tile_mma<2, 1, FOLD>(acc, wd, hbase, (unsigned)(n * F8 * 2), F8, n, smem);   // K = F / 8 <= 512
+        tile_mma<2, 1, FOLD, true>(acc, wd, hbase, (unsigned)(n * F8 * 2), F8, n, smem);   // K = F / 8 <= 512
         __syncthreads();
         tile_reduce<2>(acc, red);
 #pragma unroll
@@ -1227,7 +1235,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
         int wr[2], oc[2];
         qkv_rows(wr, oc);
         const int nl = last_layer ? 0 : l + 1;
-        prefetch_w<2>(wq, mkr(lt[nl].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
+        prefetch_w<2, false>(wq, mkr(lt[nl].wqkv, (size_t)(dq + 2 * dkv) * d * 2), d, wr);
       }
       if (!wait_flags<true>(sy, team, &flag, pk5)) return bail();
       mark();

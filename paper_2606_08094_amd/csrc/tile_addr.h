@@ -21,3 +21,19 @@ constexpr TileLoad skinny_w_at(unsigned lo, int s, int subs, unsigned k, unsigne
 constexpr TileLoad skinny_x_at(unsigned lo, int row, int xt, unsigned k, unsigned ke) {
   return k < ke && row < xt ? TileLoad{lo, (k * (unsigned)xt + (unsigned)row) * 64u} : TileLoad{kOob, 0u};
 }
+
+// Persistent kernel's team GEMMs: k-step v of the 128 k-values at kc.  TAIL:
+// K may end inside those or before them; else they all exist.
+// W tiled [rows / 16][K / 32][16][32] bf16, the 16-row block that begins at `row`.
+template <bool TAIL>
+constexpr TileLoad team_w_at(unsigned lo, int row, int kc, int v, int K) {
+  return TAIL && kc + 32 * v >= K ? TileLoad{kOob, 0u}
+                                  : TileLoad{lo + 1024u * (unsigned)v,
+                                             ((unsigned)(row >> 4) * (unsigned)(K >> 5) + (unsigned)(kc >> 5)) * 1024u};
+}
+// X [K / 32][M][32] bf16, 16-row subtile ms; lo: the lane's place in a tile, kOob in rows past M.
+template <bool TAIL>
+constexpr TileLoad team_x_at(unsigned lo, int ms, int kc, int v, int K, int M) {
+  return TAIL && kc + 32 * v >= K ? TileLoad{kOob, 0u}
+                                  : TileLoad{lo, (unsigned)(((kc >> 5) + v) * M * 64 + ms * 16 * 64)};
+}

@@ -36,6 +36,11 @@ CASES = {
     "chunk61_unfolded": SMALL.with_(name="n61", n_action=61, prefix_len=45, n_steps=2, seed_base=6500),
     "chunk64_unfolded_d1024": SMALL.with_(name="n64", d_model=1024, head_dim=128, d_ff=4096, d_prefix=1024,
                                           n_action=64, prefix_len=90, n_steps=1, seed_base=6600),
+    # a team's MLP columns (d_ff / 8) end inside a 128-wide chunk, or fill less than one
+    "d_ff_256": SMALL.with_(name="f256", d_ff=256, n_action=17, prefix_len=33, n_steps=2, seed_base=6900),
+    "d_ff_1280": SMALL.with_(name="f1280", d_ff=1280, prefix_len=64, n_steps=2, seed_base=6910),
+    "d_ff_3840_d1024": SMALL.with_(name="f3840", d_model=1024, head_dim=128, d_ff=3840, d_prefix=1024, n_action=60,
+                                   prefix_len=70, n_steps=1, seed_base=6920),
 }
 
 
@@ -185,12 +190,14 @@ def test_persist_pi0_full(torch):
     assert err <= TOL
 
 
-def test_ineligible_model_falls_back(torch):
-    """Loop mode 2 on a model the persistent kernel does not cover (fp32,
-    self + cross attention) runs the graph driver: identical output."""
-    cfg = wl.TINY_F32
+@pytest.mark.parametrize("cfg,batch", [(wl.TINY_F32, 2), (SMALL.with_(name="f640", d_ff=640, n_steps=2), 1)],
+                         ids=["fp32_self_cross", "d_ff_640"])
+def test_ineligible_model_falls_back(torch, cfg, batch):
+    """Loop mode 2 on a model the persistent kernel does not cover (fp32 with
+    self + cross attention; a d_ff whose eighths are not whole 32-wide k-steps)
+    runs the graph driver: identical output."""
     W = wl.make_weights(cfg)
-    inp = wl.make_batch(cfg, 2)
+    inp = wl.make_batch(cfg, batch)
     tau = wl.uniform_schedule(cfg.n_steps)
     a = _run(cfg, W, inp, tau, loop_mode=2, expect_persist=False)[0]
     b = _run(cfg, W, inp, tau, loop_mode=1)[0]

@@ -46,6 +46,29 @@ int main() {
                       }
                     }
           }
+  // persistent kernel: teams' W of `rows` rows and X of M rows, K cut into chunks of 128 (K <= 1024)
+  for (int K : {32, 64, 96, 128, 160, 288, 480, 512, 1024})
+    for (int kc = 0; kc < 1024; kc += 128)
+      for (int v = 0; v < 4; ++v)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int r16 = lane & 15;
+          const unsigned lo = r16 * 64 + (lane >> 4) * 16;
+          const bool k = kc + 32 * v < K;
+          for (int rows : {512, 1024})
+            for (int row : {0, rows - 16}) {
+              check("team W", team_w_at<true>(lo, row, kc, v, K), 2ull * rows * K, k, K, kc, v);
+              if (K % 512 == 0 && kc < K) check("team W", team_w_at<false>(lo, row, kc, v, K), 2ull * rows * K, true, K, kc, v);
+            }
+          for (int M : {1, 16, 17, 50, 64})
+            for (int ms = 0; ms < 4; ++ms) {
+              const bool in = 16 * ms + r16 < M;
+              const TileLoad a = team_x_at<true>(in ? lo : kOob, ms, kc, v, K, M);
+              // a subtile's rows share the uniform offset: beside lanes past M it stays the subtile's
+              if (in || !k) check("team X", a, 2ull * M * K, in && k, K, kc, v);
+              else check("team X past M", {a.lane, 0}, 2ull * M * K, false, K, kc, v);
+              if (in && K % 512 == 0 && kc < K) check("team X", team_x_at<false>(lo, ms, kc, v, K, M), 2ull * M * K, true, K, kc, v);
+            }
+        }
   return 0;
 }
 '''
