@@ -4,7 +4,10 @@
 // agent-scope fence writes back and invalidates the XCD's whole L2, so
 // in-kernel cross-workgroup reductions cost far more than a launch).
 //
-// gemm_skinny -- the per-step projections, M <= 128 token rows.
+// gemm_skinny -- the per-step projections: row-major operands up to
+//   kSkinnyRows token rows, tiled ones of any number where the planner's cost
+//   is below gemm_tile's (the caller decides both, and sees to it that X stays
+//   below 2 GiB: its loads have 32-bit offsets).
 //   A workgroup of 8 waves owns 16*NSUB rows of W (NSUB = 2: a gate/up pair
 //   of interleaved 16-row blocks), 16*MS token rows and one K-range
 //   (split-K across workgroups only where the epilogue writes partials).  The
@@ -509,9 +512,9 @@ __global__ __launch_bounds__(256) void gemm_tile_rs(GemmArgs a) {
 // flight and does not wait for those.  Requires K % 64 == 0 (rows beyond M
 // or N are loaded from a valid row and never stored).
 //
-// NWV waves: 4 in 2 x 2, or 8 in 2 x 4 (two per SIMD).  Every wave sums its
-// outputs' k-products slice by slice in the same order, so the wave layout
-// does not change a result.  The 256 x 256 tile (eight waves, 128 x 64 per
+// NWV = 8 waves, 2 x 4 (two per SIMD).  Every wave sums its
+// outputs' k-products slice by slice in the same order, so the tile does not
+// change a result.  The 256 x 256 tile (128 x 64 per
 // wave) feeds 128 FLOP per staged byte instead of 85 (256 x 128); its two
 // 64 KB stages fill the LDS, and a slice's MFMAs cover the next slice's load.
 //

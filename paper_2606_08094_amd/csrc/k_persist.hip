@@ -470,7 +470,13 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   // in the state row).  In LDS and not in a register of the first threads: a
   // value that lives through the whole loop in a few lanes was lost there in
   // some forms of this kernel (the compiler copied its register inside
-  // a one-lane branch, so only that lane kept it).
+  // a one-lane branch, so only that lane kept it).  The branches of single
+  // lanes that remain (sum2, head, the attention's stats) hold stores only,
+  // and the built code of all 18 forms was read for that fault: under a lane
+  // mask it writes no accumulator register and no scratch, where values that
+  // live through the loop are parked, and its register moves there are of
+  // values the branch itself selects.  Stores from every lane in sum2 and head
+  // instead make the 256-wide forms spill 2 to 13 registers.
   if (tid < 32)
     for (int r = 0; r < 2; ++r)
       sa[r][tid] = mok[r] && mrow[r] >= st && tid < A ? a.a0[(size_t)(mrow[r] - st) * A + tid] : 0.f;

@@ -271,8 +271,9 @@ Tiling tern_tiling(int M, int N, int K, int nsub) {
   return t;
 }
 
-// Dense GEMM launch: the skinny kernel when the shape allows (M <= 128), else
-// the tiled one (bf16) or the wide one (fp32).
+// Dense GEMM launch: the skinny kernel up to kSkinnyRows token rows, above them
+// the tiled one (bf16; or the skinny one for an unsplit projection whose
+// operands are tiled, where its cost is lower) or the wide one (fp32).
 struct DenseLaunch {
   bool skinny;
   bool tile;
