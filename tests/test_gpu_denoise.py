@@ -516,3 +516,36 @@ def test_degenerate_and_limit_shapes(torch, name, loop_mode):
     print(f"{name} (loop mode {loop_mode}): max|d| = {err:.3e} (tol {TOL[cfg.wtype]})")
     assert np.all(np.isfinite(got))
     assert err <= TOL[cfg.wtype]
+
+
+# Above 128 token rows (where the tiled GEMM kernel takes over): widths that are padded to whole 64-value slices
+# (720, 712 and 1360), gate/up projections that stay on the skinny kernel (150 rows) and ones that do not (408), the
+# state token's extra row of every request, and fp32 (136 rows).
+ROWS = {
+    "smolvla_3": (wl.SMOLVLA_BF16.with_(name="rows_3", n_layers=2, prefix_len=65, n_steps=2, seed_base=9500), 3),
+    "smolvla_8_variants": (wl.SMOLVLA_BF16.with_(name="rows_8", n_layers=2, prefix_len=33, n_steps=2, causal_self=True,
+                                                 state_token=True, seed_base=9510), 8),
+    "ragged_widths_4": (wl.SMOLVLA_BF16.with_(name="rows_4", n_layers=2, d_model=712, d_ff=1360, mlp="gelu",
+                                              prefix_len=40, n_steps=2, seed_base=9520), 4),
+    "f32_17": (wl.TINY_F32.with_(name="rows_17", n_steps=2, seed_base=9530), 17),
+}
+
+
+@pytest.mark.parametrize("name", sorted(ROWS))
+def test_many_token_rows(torch, name):
+    cfg, batch = ROWS[name]
+    W = wl.make_weights(cfg)
+    inp = wl.make_batch(cfg, batch)
+    tau = wl.uniform_schedule(cfg.n_steps)
+    cache_ref, ref = _oracle(cfg, W, inp, tau)
+    pipe = _pipe(cfg, W, inp)
+    try:
+        pipe.build_cache()
+        got = pipe.denoise(tau).cpu().numpy().astype(np.float64)
+        _check_cache(pipe, cache_ref, cfg)
+    finally:
+        pipe.close()
+    err = np.abs(got - ref).max()
+    print(f"{name}: max|d| = {err:.3e} (tol {TOL[cfg.wtype]})")
+    assert np.all(np.isfinite(got))
+    assert err <= TOL[cfg.wtype]
