@@ -25,8 +25,10 @@ extern "C" {
  * 20, 21 = variants 0 and 4 on operands in the layouts of an expert's plans
  * (both tiled, K padded to whole 64-wide slices; copies are made and freed),
  * 10..14 = the tiled kernel with tile 64x128, 128x128, 256x128, 128x256 or
- * 256x256, 22..24 = with tile 160x128, 208x128 or 208x256 (VLA_E_UNSUPPORTED
- * unless bf16 with M > 128, and for 14 and 22..24 with K % 64 != 0). */
+ * 256x256, 22..24 = with tile 160x128, 208x128 or 208x256, 25..27 = 22..24 on
+ * operands in the layouts of an expert's plans, 28..30 = 25..27 with K in two
+ * ranges whose fp32 partials are summed into y (VLA_E_UNSUPPORTED unless bf16
+ * with M > 128, for 14 and 22..24 with K % 64 != 0, for 28..30 with K <= 64). */
 vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, int32_t N, int32_t K,
                          int32_t variant, float* y, void* stream);
 

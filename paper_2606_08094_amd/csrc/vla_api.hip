@@ -1677,8 +1677,8 @@ int32_t vla_test_persist_trace(vla_model* m, uint64_t* out, int32_t max_per_team
 vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, int32_t N, int32_t K,
                          int32_t variant, float* y, void* stream) {
   if (elem != 0 && elem != 1) return fail(VLA_E_ARG, "elem must be 0 or 1");
-  if (variant < 0 || (variant > 4 && variant < 10) || (variant > 14 && variant < 20) || variant > 24)
-    return fail(VLA_E_ARG, "variant must be 0..4, 10..14 or 20..24");
+  if (variant < 0 || (variant > 4 && variant < 10) || (variant > 14 && variant < 20) || variant > 30)
+    return fail(VLA_E_ARG, "variant must be 0..4, 10..14 or 20..30");
   if (!x || !w || !y || !al16(x) || !al16(w) || !al16(y)) return fail(VLA_E_ARG, "bad buffer");
   if (M < 1 || N < 1 || K < 1 || K % (elem ? 8 : 4)) return fail(VLA_E_SHAPE, "bad GEMM shape");
   const int et = elem ? ET_BF16 : ET_F32;
@@ -1686,15 +1686,16 @@ vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, 
   GemmArgs g{};
   g.M = M; g.N = N; g.K = K; g.X = x; g.ldx = K; g.W = w;
   g.epi = EPI_STORE; g.out = y; g.ldo = N; g.out_f32 = 1;
-  struct Bufs {   // operands of variants 20 and 21, in an expert's layouts
+  struct Bufs {   // operands of variants 20, 21 and 25..30, in an expert's layouts
     void *x = nullptr, *w = nullptr;
     ~Bufs() {
       (void)hipFree(x);
       (void)hipFree(w);
     }
   } bufs;
-  if (variant > 21) variant -= 7;   // tiles 5..7
-  if (variant >= 20) {
+  const bool halves = variant >= 28;   // K in two ranges of the forced tile
+  const int want = variant;
+  if (want == 20 || want == 21 || want >= 25) {
     const int ks = kstep(et), Kp = kpad(K), kt = Kp / ks, Mp = (M + 15) / 16 * 16;
     const size_t es = esize(et);
     if (hipMalloc(&bufs.x, (size_t)Mp * Kp * es) != hipSuccess ||
@@ -1712,13 +1713,23 @@ vla_status vla_test_gemm(int32_t elem, const void* x, const void* w, int32_t M, 
       HIP_TRY(hipMemcpy2D((char*)bufs.x + (size_t)t * Mp * 64, 64, (const char*)x + (size_t)t * 64, K * es,
                           std::min(ks, K - t * ks) * es, M, hipMemcpyDeviceToDevice));
     HIP_TRY(hipDeviceSynchronize());
-    variant = variant == 21 ? 4 : 0;
   }
-  if (variant == 4) {
+  if (want == 20) variant = 0;
+  else if (want == 21) variant = 4;
+  else if (want >= 22) variant = 15 + (want - 22) % 3;   // tiles 5..7
+  if (variant == 4 || halves) {
     // the residual projections' launch: split-K fp32 partials, summed here
     g.epi = EPI_PARTIAL;
-    const DenseLaunch d = dense_launch(et, g, 1, 0);
+    DenseLaunch d = dense_launch(et, g, 1, halves ? variant : 0);
     if (!d.skinny && !d.tile) return fail(VLA_E_UNSUPPORTED, "no split-K launch for this shape");
+    if (halves) {
+      const int slices = g.K / 64;
+      if (slices < 2) return fail(VLA_E_UNSUPPORTED, "one K slice");
+      d.tl.nsplit = 2;
+      d.tl.kper = cdiv(slices, 2) * 64;
+      d.tl.units = d.tl.m_tiles * d.tl.n_tiles * 2;
+      d.tl.grid = cdiv(d.tl.units, 8) * 8;
+    }
     float* part = nullptr;
     if (hipMalloc(reinterpret_cast<void**>(&part), (size_t)d.splits() * M * N * sizeof(float)) != hipSuccess)
       return fail(VLA_E_NOMEM, "gemm partials");

@@ -44,6 +44,8 @@ GEMM_SHAPES = [
     (100, 1024, 4096), (90, 1000, 4096), (120, 1536, 3072),
     # large M (batched requests, prefix K/V build): the tiled kernel, ragged in M, N and K
     (400, 1024, 4096), (1600, 2560, 1024), (257, 136, 72), (300, 100, 200), (520, 200, 640),
+    # the planner's own split (variants 4 and 21) of a 160-row tile: three ranges, a short last partial pass
+    (1284, 1024, 4096),
 ]
 
 # 0 runtime choice, 1 wide, 2 skinny, 3 tiled (runtime tile), 4 split-K partials (the residual
@@ -78,12 +80,15 @@ def test_gemm_parity(torch, elem, M, N, K):
         assert np.all(err <= bound), f"variant={variant} max err {err.max()} worst ratio {(err / bound).max()}"
 
 
-@pytest.mark.parametrize("variant", [22, 23, 24])
+@pytest.mark.parametrize("variant", [22, 23, 24, 25, 26, 27, 28, 29, 30])
 @pytest.mark.parametrize("M,N,K", [(129, 128, 64), (160, 130, 128), (161, 256, 192), (208, 257, 320), (209, 64, 1024),
                                    (416, 384, 256), (417, 100, 64), (816, 512, 2048)])
 def test_gemm_tile_heights(torch, M, N, K, variant):
     """Tiles of 160 and 208 rows (an odd number of 16-row subtiles: one row of waves holds one more): last tiles
-    of 1, 16 and all rows, ragged columns, one K slice to many."""
+    of 1, 16 and all rows, ragged columns, one K slice to many.  22..24 row-major operands, 25..27 tiled ones, 28..30
+    tiled ones in two K ranges, whose partials leave through LDS in passes that a tile's height does not divide."""
+    if variant >= 28 and K <= 64:
+        pytest.skip("one K slice does not split")
     seed = 1000 * M + N + K
     x = wl.random_matrix((M, K), seed, 1.0, bf16=True)
     w = wl.random_matrix((N, K), seed + 1, 0.05, bf16=True)
