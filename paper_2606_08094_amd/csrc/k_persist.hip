@@ -196,7 +196,8 @@ struct WTile {
 };
 
 // W: tiled [rows / 16][K / 32][16][32] bf16 (rsrc over the matrix); wrow[s] < 0: tile s absent.
-// TAIL: K may end inside a chunk, whose k-steps past it are zero like absent chunks.
+// TAIL: K may end inside a chunk, whose k-steps past it are zero like absent
+// chunks; else K is in whole chunks.
 template <int NS, bool TAIL>
 VLA_DEV void prefetch_w(WTile<NS>& t, rsrc_t W, int K, const int (&wrow)[NS]) {
   // the wave index in a scalar register: the row-block offsets derived from it
@@ -387,7 +388,9 @@ size_t lds_main(int hd) {
 // plain expert's kernel, which uses nearly every register, carries none of it;
 // always unfolded (the pi0-shaped state token makes 51 rows).  A pi0-shaped
 // chunk with all three over 571 prefix rows: 6.11 ms, against 10.5 ms as
-// about 1640 launches of a graph.
+// about 1640 launches of a graph.  It also takes a d_ff whose eighths end
+// inside a chunk of 128 (no plain expert here has one): the checks of the down
+// projection's weight loads cost the plain kernel 2% at 4 to 20 rows.
 template <int HD, int DPT, bool FOLD, bool VAR>
 __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   using L = PLds<HD>;
@@ -1208,7 +1211,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         dn_rows(wr);
-        prefetch_w<2, true>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
+        prefetch_w<2, VAR>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
       }
       if (!wait_flags<false>(sy, team, &flag, pk4)) return bail();
       mark();
@@ -1318,6 +1321,7 @@ const void* persist_fn_t(int hd, int dpt) {
     default: return nullptr;
   }
 }
+// var: an architecture variant, or a team's MLP columns not in whole chunks;
 // plain chunks of at most 50 rows take the folded-tail form of the GEMM phases
 const void* persist_fn(int hd, int d, int n, bool var) {
   const int dpt = d / NTHR;
@@ -1348,7 +1352,7 @@ bool persist_resident(int d, int hd, int HT) {
 hipError_t launch_persist(const PersistArgs& a, hipStream_t s) {
   const size_t lds = persist_lds_bytes(a.hd, a.HT);
   void* args[] = {const_cast<PersistArgs*>(&a)};
-  const void* fn = persist_fn(a.hd, a.d, a.n, a.causal || a.stok || a.rot != nullptr);
+  const void* fn = persist_fn(a.hd, a.d, a.n, a.causal || a.stok || a.rot != nullptr || a.F % 1024 != 0);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

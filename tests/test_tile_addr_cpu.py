@@ -57,7 +57,7 @@ int main() {
           for (int rows : {512, 1024})
             for (int row : {0, rows - 16}) {
               check("team W", team_w_at<true>(lo, row, kc, v, K), 2ull * rows * K, k, K, kc, v);
-              if (K % 512 == 0 && kc < K) check("team W", team_w_at<false>(lo, row, kc, v, K), 2ull * rows * K, true, K, kc, v);
+              if (K % 128 == 0 && kc < K) check("team W", team_w_at<false>(lo, row, kc, v, K), 2ull * rows * K, true, K, kc, v);
             }
           for (int M : {1, 16, 17, 50, 64})
             for (int ms = 0; ms < 4; ++ms) {
