@@ -388,10 +388,11 @@ size_t lds_main(int hd) {
 // plain expert's kernel, which uses nearly every register, carries none of it;
 // always unfolded (the pi0-shaped state token makes 51 rows).  A pi0-shaped
 // chunk with all three over 571 prefix rows: 6.11 ms, against 10.5 ms as
-// about 1640 launches of a graph.  It also takes a d_ff whose eighths end
-// inside a chunk of 128 (no plain expert here has one): the checks of the down
-// projection's weight loads cost the plain kernel 2% at 4 to 20 rows.
-template <int HD, int DPT, bool FOLD, bool VAR>
+// about 1640 launches of a graph.
+// TAIL: a team's MLP columns (d_ff / 8) may end inside a chunk of 128.  A form
+// of its own for plain experts: the checks of the down projection's weight
+// loads cost a pi0-shaped chunk of 4 to 20 rows 2%.
+template <int HD, int DPT, bool FOLD, bool VAR, bool TAIL>
 __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   using L = PLds<HD>;
   constexpr int VPR = HD / 8;              // 16-byte vectors per K/V row
@@ -475,7 +476,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
   // some forms of this kernel (the compiler copied its register inside
   // a one-lane branch, so only that lane kept it).  The branches of single
   // lanes that remain (sum2, head, the attention's stats) hold stores only,
-  // and the built code of all 18 forms was read for that fault: under a lane
+  // and the built code of all 30 forms was read for that fault: under a lane
   // mask it writes no accumulator register and no scratch, where values that
   // live through the loop are parked, and its register moves there are of
   // values the branch itself selects.  Stores from every lane in sum2 and head
@@ -1211,7 +1212,7 @@ __global__ __launch_bounds__(NTHR, 1) void persist_kernel(PersistArgs a) {
       {
         int wr[2];
         dn_rows(wr);
-        prefetch_w<2, VAR>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
+        prefetch_w<2, TAIL>(wd, mkr((const bf16_t*)ly.wd + (size_t)team * d * F8, (size_t)d * F8 * 2), F8, wr);
       }
       if (!wait_flags<false>(sy, team, &flag, pk4)) return bail();
       mark();
@@ -1309,29 +1310,29 @@ size_t persist_lds_bytes(int hd, int HT) {
 }
 
 namespace {
-template <bool FOLD, bool VAR>
+template <bool FOLD, bool VAR, bool TAIL>
 const void* persist_fn_t(int hd, int dpt) {
   switch (hd * 10 + dpt) {
-    case 2564: return reinterpret_cast<const void*>(&persist_kernel<256, 4, FOLD, VAR>);
-    case 2562: return reinterpret_cast<const void*>(&persist_kernel<256, 2, FOLD, VAR>);
-    case 1284: return reinterpret_cast<const void*>(&persist_kernel<128, 4, FOLD, VAR>);
-    case 1282: return reinterpret_cast<const void*>(&persist_kernel<128, 2, FOLD, VAR>);
-    case 644: return reinterpret_cast<const void*>(&persist_kernel<64, 4, FOLD, VAR>);
-    case 642: return reinterpret_cast<const void*>(&persist_kernel<64, 2, FOLD, VAR>);
+    case 2564: return reinterpret_cast<const void*>(&persist_kernel<256, 4, FOLD, VAR, TAIL>);
+    case 2562: return reinterpret_cast<const void*>(&persist_kernel<256, 2, FOLD, VAR, TAIL>);
+    case 1284: return reinterpret_cast<const void*>(&persist_kernel<128, 4, FOLD, VAR, TAIL>);
+    case 1282: return reinterpret_cast<const void*>(&persist_kernel<128, 2, FOLD, VAR, TAIL>);
+    case 644: return reinterpret_cast<const void*>(&persist_kernel<64, 4, FOLD, VAR, TAIL>);
+    case 642: return reinterpret_cast<const void*>(&persist_kernel<64, 2, FOLD, VAR, TAIL>);
     default: return nullptr;
   }
 }
-// var: an architecture variant, or a team's MLP columns not in whole chunks;
 // plain chunks of at most 50 rows take the folded-tail form of the GEMM phases
-const void* persist_fn(int hd, int d, int n, bool var) {
+const void* persist_fn(int hd, int d, int F, int n, bool var) {
   const int dpt = d / NTHR;
-  if (var) return persist_fn_t<false, true>(hd, dpt);
-  return n <= 50 ? persist_fn_t<true, false>(hd, dpt) : persist_fn_t<false, false>(hd, dpt);
+  if (var) return persist_fn_t<false, true, true>(hd, dpt);
+  if (F % 1024 != 0) return n <= 50 ? persist_fn_t<true, false, true>(hd, dpt) : persist_fn_t<false, false, true>(hd, dpt);
+  return n <= 50 ? persist_fn_t<true, false, false>(hd, dpt) : persist_fn_t<false, false, false>(hd, dpt);
 }
 }  // namespace
 
-bool persist_resident(int d, int hd, int HT) {
-  const void* fns[3] = {persist_fn(hd, d, 1, false), persist_fn(hd, d, 64, false), persist_fn(hd, d, 1, true)};
+bool persist_resident(int d, int hd, int HT, int F) {
+  const void* fns[3] = {persist_fn(hd, d, F, 1, false), persist_fn(hd, d, F, 64, false), persist_fn(hd, d, F, 1, true)};
   int dev = 0, cus = 0, nb = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus != NWG)
@@ -1352,7 +1353,7 @@ bool persist_resident(int d, int hd, int HT) {
 hipError_t launch_persist(const PersistArgs& a, hipStream_t s) {
   const size_t lds = persist_lds_bytes(a.hd, a.HT);
   void* args[] = {const_cast<PersistArgs*>(&a)};
-  const void* fn = persist_fn(a.hd, a.d, a.n, a.causal || a.stok || a.rot != nullptr || a.F % 1024 != 0);
+  const void* fn = persist_fn(a.hd, a.d, a.F, a.n, a.causal || a.stok || a.rot != nullptr);
   if (!fn) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

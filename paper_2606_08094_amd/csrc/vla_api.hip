@@ -485,7 +485,7 @@ bool persist_eligible(vla_model* m, int B, int P, int T) {
                         persist_supported(m->d, c.head_dim, c.n_heads, c.n_kv_heads, c.d_ff,
                                           c.n_action + (m->state_token ? 1 : 0), P, c.d_action, c.mlp != VLA_MLP_GELU, &kba, &nsplit);
   if (!shape_ok) return false;
-  if (m->persist_dev_ok < 0) m->persist_dev_ok = persist_resident(m->d, c.head_dim, c.n_heads / 8) ? 1 : 0;
+  if (m->persist_dev_ok < 0) m->persist_dev_ok = persist_resident(m->d, c.head_dim, c.n_heads / 8, c.d_ff) ? 1 : 0;
   return m->persist_dev_ok == 1;
 }
 

@@ -302,6 +302,6 @@ hipError_t launch_rope(int et, void* x, int rows, int rpr, int ld, int col0, int
 bool persist_supported(int d, int hd, int H, int G, int F, int n, int P, int A, int glu, int* kba, int* nsplit);
 // The device can hold every workgroup of the persistent kernel at once (its
 // 256 workgroups, one per compute unit, 32 on each of the 8 XCDs).
-bool persist_resident(int d, int hd, int HT);
+bool persist_resident(int d, int hd, int HT, int F);
 size_t persist_lds_bytes(int hd, int HT);
 hipError_t launch_persist(const PersistArgs& a, hipStream_t s);

@@ -116,6 +116,8 @@ VARIANTS = {
                                 rope_base=10000.0, state_token=True, seed_base=6800),
     "all_30_d1024_hd64": SMALL.with_(name="v_a30", d_model=1024, d_ff=4096, d_prefix=1024, n_action=30, prefix_len=77,
                                      n_steps=2, causal_self=True, rope_base=10000.0, state_token=True, seed_base=6810),
+    "all_30_d_ff_1280": SMALL.with_(name="v_f1280", d_ff=1280, n_action=30, prefix_len=50, n_steps=2, causal_self=True,
+                                    rope_base=10000.0, state_token=True, seed_base=6820),
     "all_63_d1024": SMALL.with_(name="v_a63", d_model=1024, head_dim=128, d_ff=4096, d_prefix=1024, n_action=63,
                                 prefix_len=97, n_steps=2, causal_self=True, rope_base=10000.0, state_token=True,
                                 seed_base=6790),
