@@ -523,6 +523,9 @@ __global__ __launch_bounds__(256) void gemm_tile_rs(GemmArgs a) {
 // so an odd MR loads the four SIMDs evenly.  A height that divides the rows
 // well saves the work of padding: 816 rows in four 208-row tiles instead of
 // four of 256, 1600 in eight instead of seven that fill fewer compute units.
+// 160 and 208 are the two heights between the powers of two that were built
+// and measured; the planner weighs every tile by its cost, so a row count that
+// neither divides well takes the one with the least padding and rounds.
 template <int MR, int NS, int NWV>
 struct Ring {
   static constexpr int BM = 16 * MR, BN = 32 * NS, ROWS = BM + BN;
